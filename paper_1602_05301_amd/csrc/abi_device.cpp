@@ -478,8 +478,9 @@ qbx_status upload(qbx_geom_s *G)
 
     // translation tables, [in][out] (column of the scaled matrix per input index)
     std::vector<cd> m2m, l2l, m2l;
-    std::vector<long long> m2m_off(4 * (size_t)std::max(pl.nlev, 1), -1),
-        l2l_off(4 * (size_t)std::max(pl.nlev, 1), -1), m2l_off(40 * (size_t)std::max(pl.nlev, 1), -1);
+    std::vector<RowBlk> rblk;
+    std::vector<int> m2m_rb0(4 * (size_t)std::max(pl.nlev, 1), -1),
+        l2l_rb0(4 * (size_t)std::max(pl.nlev, 1), -1), m2l_rb0(40 * (size_t)std::max(pl.nlev, 1), -1);
     // V-list positions: target box, grouping by (level, offset), output rows
     int nv = (int)pl.V_idx.size();
     std::vector<int> vtgt(nv), vpos(nv);
@@ -556,39 +557,69 @@ qbx_status upload(qbx_geom_s *G)
         g.m2l_rot = ar.upload(rot);
     }
     // Row-major [out][in] matrix -> v_mfma_f64_16x16x4f64 A-operand order:
-    // 16x4 blocks of 64 values, block (rb, kb) at (rb * NK + kb) * 64, lane l
-    // holding element (rb*16 + l%16, kb*4 + l/16), zero outside the matrix.
-    auto append_tiled = [](std::vector<cd> &dst, const std::vector<std::complex<double>> &M, int nout,
-                           int nin) {
-        int NR = (nout + 15) / 16, NK = (nin + 3) / 4;
-        long long off = (long long)dst.size();
-        dst.resize(dst.size() + (size_t)NR * NK * 64, mk(0.0, 0.0));
-        for (int rb = 0; rb < NR; ++rb)
-            for (int kb = 0; kb < NK; ++kb)
+    // 16x4 blocks of 64 values, lane l of block (rb, kb) holding element
+    // (rb*16 + l%16, kb*4 + l/16), zero outside the matrix; per row block the
+    // run of kept blocks.  Returns the first row block.
+    bool table_ok = true;
+    auto append_tiled = [&](std::vector<cd> &dst, int nout, int nin, const KeptRows &kr, auto matrix) {
+        std::vector<std::complex<double>> M;
+        if (!ar.sizing) M = matrix();      // the sizing pass needs the shapes only
+        int NR = (nout + 15) / 16, first = (int)rblk.size();
+        for (int rb = 0; rb < NR; ++rb) {
+            size_t off = dst.size();
+            RowBlk d{(int)(off / 64), nin, 0, 0};
+            for (int r = rb * 16; r < std::min(nout, rb * 16 + 16); ++r) {
+                d.k0 = std::min(d.k0, kr.lo[r] / 4);
+                d.k1 = std::max(d.k1, kr.hi[r] / 4 + 1);
+            }
+            table_ok = table_ok && off / 64 <= 0x7fffffff;
+            rblk.push_back(d);
+            dst.resize(off + (size_t)(d.k1 - d.k0) * 64, mk(0.0, 0.0));
+            for (int kb = d.k0; kb < d.k1 && !ar.sizing; ++kb)
                 for (int lane = 0; lane < 64; ++lane) {
                     int row = rb * 16 + lane % 16, k = kb * 4 + lane / 16;
                     if (row < nout && k < nin) {
                         const auto &v = M[(size_t)row * nin + k];
-                        dst[off + ((size_t)rb * NK + kb) * 64 + lane] = mk(v.real(), v.imag());
+                        dst[off + (size_t)(kb - d.k0) * 64 + lane] = mk(v.real(), v.imag());
                     }
                 }
-        return off;
+        }
+        return first;
     };
     if (!pl.opt.direct) {
-        for (int l = 2; l + 1 < pl.nlev; ++l)
+        for (int l = 2; l + 1 < pl.nlev; ++l) {
+            KeptRows up = m2m_kept(pl, l), down = l2l_kept(pl, l);
             for (int q = 0; q < 4; ++q) {
                 int np = 2 * pl.P[l] + 1, nc = 2 * pl.P[l + 1] + 1;
-                m2m_off[l * 4 + q] = append_tiled(m2m, m2m_matrix(pl, l, q), np, nc);
-                l2l_off[l * 4 + q] = append_tiled(l2l, l2l_matrix(pl, l, q), nc, np);
+                m2m_rb0[l * 4 + q] = append_tiled(m2m, np, nc, up, [&] { return m2m_matrix(pl, l, q, up); });
+                l2l_rb0[l * 4 + q] = append_tiled(l2l, nc, np, down, [&] { return l2l_matrix(pl, l, q, down); });
             }
+        }
+        // the groups are sorted by level; offsets at one distance keep alike
+        std::vector<int> d2;
+        std::vector<KeptRows> kept;
+        int at = -1;
         for (const auto &grp : G->m2l_groups) {
             int l = grp.key / 40, o = grp.key % 40;
             int dx, dy;
             v_offset_from_id(o, &dx, &dy);
+            if (l != at) {
+                at = l;
+                d2.clear();
+                for (const auto &h : G->m2l_groups) {
+                    if (h.key / 40 != l) continue;
+                    int x, y;
+                    v_offset_from_id(h.key % 40, &x, &y);
+                    if (std::find(d2.begin(), d2.end(), x * x + y * y) == d2.end()) d2.push_back(x * x + y * y);
+                }
+                kept = m2l_kept(pl, l, d2);
+            }
+            const KeptRows &kr = kept[std::find(d2.begin(), d2.end(), dx * dx + dy * dy) - d2.begin()];
             int n = 2 * pl.P[l] + 1;
-            m2l_off[grp.key] = append_tiled(m2l, m2l_matrix(pl, l, dx, dy), n, n);
+            m2l_rb0[grp.key] = append_tiled(m2l, n, n, kr, [&] { return m2l_matrix(pl, l, dx, dy, kr); });
         }
     }
+    if (!table_ok) return fail(QBX_E_NOMEM, "translation tables too large");
     g.m2m_mf = ar.upload(m2m); g.l2l_mf = ar.upload(l2l); g.m2l_mf = ar.upload(m2l);
     g.far32 = pl.opt.far_fp32 ? 1 : 0;
     g.m2l_mf32 = g.l2l_mf32 = nullptr;
@@ -602,7 +633,8 @@ qbx_status upload(qbx_geom_s *G)
         g.m2l_mf32 = ar.upload(to32(m2l));
         g.l2l_mf32 = ar.upload(to32(l2l));
     }
-    g.m2m_mf_off = ar.upload(m2m_off); g.l2l_mf_off = ar.upload(l2l_off); g.m2l_mf_off = ar.upload(m2l_off);
+    g.rblk = ar.upload(rblk);
+    g.m2m_rb0 = ar.upload(m2m_rb0); g.l2l_rb0 = ar.upload(l2l_rb0); g.m2l_rb0 = ar.upload(m2l_rb0);
 
     // children by quadrant; M2M parent lists and L2L child lists per level
     {

@@ -371,9 +371,10 @@ __global__ void __launch_bounds__(256) k_down_all(DevGeom g, int nd, const cd *v
 }
 
 // Part of one 16x16 output block of a scaled translation on FP64 MFMA: rows
-// rb*16.. (Arow points at the row block), k-blocks [kb0, kb1), the lane's
-// column given by bptr (nin complex inputs, NULL = 0).  The table is in
-// A-operand order (see k_m2l_mfma).  Operands of the next TB_U k-blocks are
+// rb*16.., k-blocks [kb0, kb1) (kept ones; Arow points where the row's block 0
+// would be), the lane's column at bs (nin complex inputs; bvalid false: zeros,
+// bs any readable run of nin values).  The table is in A-operand order (see
+// k_m2l_mfma).  Operands of the next TB_U k-blocks are
 // loaded while the current ones go through the matrix core.
 // z i^e (e taken mod 4): a swap and sign changes, exact
 __device__ __forceinline__ cd mul_ipow(cd z, int e)
@@ -381,6 +382,11 @@ __device__ __forceinline__ cd mul_ipow(cd z, int e)
     bool sw = e & 1, ng = e & 2;
     double re = sw ? -z.y : z.x, im = sw ? z.x : z.y;
     return ng ? mk(-re, -im) : mk(re, im);
+}
+
+__device__ __forceinline__ RowBlk load_rblk(const DevGeom &g, int i)
+{
+    return RowBlk{g.rblk[i].off, g.rblk[i].k0, g.rblk[i].k1, 0};
 }
 
 __device__ __forceinline__ void tb_load(const cd *Arow, int kb, int kb1, const cd *bs, bool bvalid,
@@ -444,12 +450,10 @@ __device__ __forceinline__ void tb_mfma(const cd *a, const cd *b, Acc3 &y, int e
 
 // Two register sets alternate: one is multiplied while the other loads.
 template <bool ROT = false>
-__device__ __forceinline__ void trans_block(const cd *Arow, int kb0, int kb1, const cd *bptr, int nin,
+__device__ __forceinline__ void trans_block(const cd *Arow, int kb0, int kb1, const cd *bs, bool bvalid, int nin,
                                             int lane, d4 &yr, d4 &yi, int rot = 0, int P = 0)
 {
     if (kb0 >= kb1) return;
-    const cd *bs = bptr ? bptr : Arow;          // any readable address when the column is empty
-    bool bvalid = bptr != nullptr;
     cd a0[TB_U], b0[TB_U], a1[TB_U], b1[TB_U];
     Acc3 y = cplx3_zero();
     int e = rot * ((lane >> 4) - P);            // order k = 4 kb + lane/16 - P
@@ -500,33 +504,35 @@ __device__ __forceinline__ void m2l_mfma_body(const DevGeom &g, int nd, const M2
             X[k * M2L_XS + sc] = (col && k < n) ? mul_ipow(col[k], rot * (k - P)) : mk(0.0, 0.0);
     }
     __syncthreads();
-    const cd *A = g.m2l_mf + g.m2l_mf_off[t.lo];
+    const auto *rbd = g.rblk + g.m2l_rb0[t.lo];
     for (int rb = wave; rb < NR; rb += nw) {
-        const cd *Ab = A + (long long)rb * NK * 64 + lane;
+        const int k0 = rbd[rb].k0, NB = rbd[rb].k1 - k0;    // kept blocks of the row block (at least one)
+        const cd *Ab = g.m2l_mf + (long long)rbd[rb].off * 64 + lane;
+        const cd *Xb = X + (k0 * 4 + bk) * M2L_XS + bc;
         Acc3 y = cplx3_zero();
         cd a0[TB_U], a1[TB_U];
 #pragma unroll
-        for (int u = 0; u < TB_U; ++u) a0[u] = Ab[min(u, NK - 1) * 64];
-        for (int kb = 0; kb < NK; kb += 2 * TB_U) {
+        for (int u = 0; u < TB_U; ++u) a0[u] = Ab[min(u, NB - 1) * 64];
+        for (int kb = 0; kb < NB; kb += 2 * TB_U) {
 #pragma unroll
-            for (int u = 0; u < TB_U; ++u) a1[u] = Ab[min(kb + TB_U + u, NK - 1) * 64];
+            for (int u = 0; u < TB_U; ++u) a1[u] = Ab[min(kb + TB_U + u, NB - 1) * 64];
             QBX_LOADS_AHEAD();
 #pragma unroll
             for (int u = 0; u < TB_U; ++u) {
                 int kk = kb + u;
-                cd bv = X[(min(kk, NK - 1) * 4 + bk) * M2L_XS + bc];
-                if (kk >= NK) bv = mk(0.0, 0.0);
+                cd bv = Xb[min(kk, NB - 1) * 4 * M2L_XS];
+                if (kk >= NB) bv = mk(0.0, 0.0);
                 cplx3_mfma(a0[u], bv, y);
             }
 #pragma unroll
-            for (int u = 0; u < TB_U; ++u) a0[u] = Ab[min(kb + 2 * TB_U + u, NK - 1) * 64];
+            for (int u = 0; u < TB_U; ++u) a0[u] = Ab[min(kb + 2 * TB_U + u, NB - 1) * 64];
             QBX_LOADS_AHEAD();
-            if (kb + TB_U < NK) {
+            if (kb + TB_U < NB) {
 #pragma unroll
                 for (int u = 0; u < TB_U; ++u) {
                     int kk = kb + TB_U + u;
-                    cd bv = X[(min(kk, NK - 1) * 4 + bk) * M2L_XS + bc];
-                    if (kk >= NK) bv = mk(0.0, 0.0);
+                    cd bv = Xb[min(kk, NB - 1) * 4 * M2L_XS];
+                    if (kk >= NB) bv = mk(0.0, 0.0);
                     cplx3_mfma(a1[u], bv, y);
                 }
             }
@@ -563,16 +569,17 @@ __device__ __forceinline__ void m2l_mfma_direct_body(const DevGeom &g, int nd, c
     int rb = c % nrmax;
     int l = t.lo / 40;
     int P = g.Plev[l], n = 2 * P + 1;
-    int NK = (n + 3) / 4, NR = (n + 15) / 16;
+    int NR = (n + 15) / 16;
     if (rb >= NR) return;
+    const RowBlk rk = load_rblk(g, g.m2l_rb0[t.lo] + rb);
     int lane = threadIdx.x;
     int bk = lane >> 4, bc = lane & 15;
     int col = t.col0 + bc;
     bool valid = bc < t.ncol;
-    const cd *bptr = valid ? mp + g.m2l_src[t.pair_start + col / nd] * nd + (long long)(col % nd) * n : nullptr;
+    const cd *bs = valid ? mp + g.m2l_src[t.pair_start + col / nd] * nd + (long long)(col % nd) * n : mp;
     int rot = valid ? g.m2l_rot[t.pair_start + col / nd] : 0;
     d4 yr = {0.0, 0.0, 0.0, 0.0}, yi = {0.0, 0.0, 0.0, 0.0};
-    trans_block<true>(g.m2l_mf + g.m2l_mf_off[t.lo] + (long long)rb * NK * 64, 0, NK, bptr, n, lane, yr, yi,
+    trans_block<true>(g.m2l_mf + ((long long)rk.off - rk.k0) * 64, rk.k0, rk.k1, bs, valid, n, lane, yr, yi,
                       rot, P);
     if (!valid) return;
     cd *o = vy + g.m2l_dst[t.pair_start + col / nd] * nd + (long long)(col % nd) * n;
@@ -637,12 +644,10 @@ __device__ __forceinline__ void tb_mfma32(const cf *a, const cf *b, Acc3f &y, in
 }
 
 template <bool ROT = false>
-__device__ __forceinline__ void trans_block32(const cf *Arow, int kb0, int kb1, const cd *bptr, int nin,
+__device__ __forceinline__ void trans_block32(const cf *Arow, int kb0, int kb1, const cd *bs, bool bvalid, int nin,
                                               int lane, f4 &yr, f4 &yi, int rot = 0, int P = 0)
 {
     if (kb0 >= kb1) return;
-    const cd *bs = bptr ? bptr : reinterpret_cast<const cd *>(Arow);
-    bool bvalid = bptr != nullptr;
     cf a0[TB_U], b0[TB_U], a1[TB_U], b1[TB_U];
     Acc3f y{{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     int e = rot * ((lane >> 4) - P);            // order k = 4 kb + lane/16 - P
@@ -669,16 +674,17 @@ __device__ __forceinline__ void m2l_mfma32_body(const DevGeom &g, int nd, const 
     int rb = c % nrmax;
     int l = t.lo / 40;
     int P = g.Plev[l], n = 2 * P + 1;
-    int NK = (n + 3) / 4, NR = (n + 15) / 16;
+    int NR = (n + 15) / 16;
     if (rb >= NR) return;
+    const RowBlk rk = load_rblk(g, g.m2l_rb0[t.lo] + rb);
     int lane = threadIdx.x;
     int bk = lane >> 4, bc = lane & 15;
     int col = t.col0 + bc;
     bool valid = bc < t.ncol;
-    const cd *bptr = valid ? mp + g.m2l_src[t.pair_start + col / nd] * nd + (long long)(col % nd) * n : nullptr;
+    const cd *bs = valid ? mp + g.m2l_src[t.pair_start + col / nd] * nd + (long long)(col % nd) * n : mp;
     int rot = valid ? g.m2l_rot[t.pair_start + col / nd] : 0;
     f4 yr = {0.f, 0.f, 0.f, 0.f}, yi = {0.f, 0.f, 0.f, 0.f};
-    trans_block32<true>(g.m2l_mf32 + g.m2l_mf_off[t.lo] + (long long)rb * NK * 64, 0, NK, bptr, n, lane, yr, yi,
+    trans_block32<true>(g.m2l_mf32 + ((long long)rk.off - rk.k0) * 64, rk.k0, rk.k1, bs, valid, n, lane, yr, yi,
                         rot, P);
     if (!valid) return;
     cd *o = vy + g.m2l_dst[t.pair_start + col / nd] * nd + (long long)(col % nd) * n;
@@ -693,12 +699,12 @@ __global__ void __launch_bounds__(64) k_m2l_mfma32(DevGeom g, int nd, const M2LT
     m2l_mfma32_body(g, nd, tiles, nrmax, mp, vy, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
-// k-block range of part h of NK split in KS near-equal parts
-__device__ __forceinline__ void ksplit(int NK, int KS, int h, int *kb0, int *kb1)
+// Part h of the k-blocks [k0, k1) split in KS near-equal parts
+__device__ __forceinline__ void ksplit(int k0, int k1, int KS, int h, int *kb0, int *kb1)
 {
-    int c = (NK + KS - 1) / KS;
-    *kb0 = min(NK, h * c);
-    *kb1 = min(NK, *kb0 + c);
+    int c = (k1 - k0 + KS - 1) / KS;
+    *kb0 = min(k1, k0 + h * c);
+    *kb1 = min(k1, *kb0 + c);
 }
 
 // Partial 16x16 blocks of the waves of one workgroup: element i of lane l is
@@ -734,19 +740,18 @@ __device__ __forceinline__ void m2m_mfma_body(const DevGeom &g, int nd, int l, c
     int rb = bid.y;
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6, q = w & 3, h = w >> 2;
     int np = 2 * g.Plev[l] + 1, nc = 2 * g.Plev[l + 1] + 1;
-    int NKc = (nc + 3) / 4;
+    const RowBlk rk = load_rblk(g, g.m2m_rb0[l * 4 + q] + rb);
     int bc = lane & 15;
     int col = t.col0 + bc;
     bool valid = bc < t.ncol;
     int d = col % nd;
     long long coff = valid ? g.m2m_coff[(long long)(t.start + col / nd) * 4 + q] : -1;
-    const cd *bptr = coff >= 0 ? mp + coff * nd + (long long)d * nc : nullptr;
+    const cd *bs = coff >= 0 ? mp + coff * nd + (long long)d * nc : mp;
     d4 yr = {0.0, 0.0, 0.0, 0.0}, yi = {0.0, 0.0, 0.0, 0.0};
     int kb0, kb1;
-    ksplit(NKc, M2M_KS, h, &kb0, &kb1);
+    ksplit(rk.k0, rk.k1, M2M_KS, h, &kb0, &kb1);
     if (__any(coff >= 0))
-        trans_block(g.m2m_mf + g.m2m_mf_off[l * 4 + q] + (long long)rb * NKc * 64, kb0, kb1, bptr, nc,
-                    lane, yr, yi);
+        trans_block(g.m2m_mf + ((long long)rk.off - rk.k0) * 64, kb0, kb1, bs, coff >= 0, nc, lane, yr, yi);
     tb_store(part[w], lane, yr, yi);
     __syncthreads();
     int tid = threadIdx.x;
@@ -779,12 +784,12 @@ __device__ __forceinline__ void l2l_mfma_body(const DevGeom &g, int nd, int L, c
     int rb = bid.y;
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int nc = 2 * g.Plev[L] + 1, np = 2 * g.Plev[L - 1] + 1;
-    int NKp = (np + 3) / 4;
+    const RowBlk rk = load_rblk(g, g.l2l_rb0[(L - 1) * 4 + t.q] + rb);
     int bc = lane & 15;
     int col = t.col0 + bc;
     bool valid = bc < t.ncol;
     int d = col % nd;
-    const cd *bptr = valid ? loc + g.l2l_poff[t.start + col / nd] * nd + (long long)d * np : nullptr;
+    const cd *bs = valid ? loc + g.l2l_poff[t.start + col / nd] * nd + (long long)d * np : loc;
     // The child's local that this thread completes, loaded ahead of the
     // K loop (it is not written in this launch: the loop reads the
     // parents' level), so that its round trip overlaps the loop.
@@ -798,9 +803,8 @@ __device__ __forceinline__ void l2l_mfma_body(const DevGeom &g, int nd, int L, c
     cd acc = own ? loc[base] : mk(0.0, 0.0);
     d4 yr = {0.0, 0.0, 0.0, 0.0}, yi = {0.0, 0.0, 0.0, 0.0};
     int kb0, kb1;
-    ksplit(NKp, L2L_KS, w, &kb0, &kb1);
-    trans_block(g.l2l_mf + g.l2l_mf_off[(L - 1) * 4 + t.q] + (long long)rb * NKp * 64, kb0, kb1, bptr,
-                np, lane, yr, yi);
+    ksplit(rk.k0, rk.k1, L2L_KS, w, &kb0, &kb1);
+    trans_block(g.l2l_mf + ((long long)rk.off - rk.k0) * 64, kb0, kb1, bs, valid, np, lane, yr, yi);
     tb_store(part[w], lane, yr, yi);
     __syncthreads();
     if (!own) return;
@@ -836,12 +840,12 @@ __device__ __forceinline__ void l2l_mfma32_body(const DevGeom &g, int nd, int L,
     int rb = bid.y;
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int nc = 2 * g.Plev[L] + 1, np = 2 * g.Plev[L - 1] + 1;
-    int NKp = (np + 3) / 4;
+    const RowBlk rk = load_rblk(g, g.l2l_rb0[(L - 1) * 4 + t.q] + rb);
     int bc = lane & 15;
     int col = t.col0 + bc;
     bool valid = bc < t.ncol;
     int d = col % nd;
-    const cd *bptr = valid ? loc + g.l2l_poff[t.start + col / nd] * nd + (long long)d * np : nullptr;
+    const cd *bs = valid ? loc + g.l2l_poff[t.start + col / nd] * nd + (long long)d * np : loc;
     // the child's local this thread completes, loaded ahead of the K loop
     int r = threadIdx.x >> 4, c = threadIdx.x & 15;
     int row = rb * 16 + r;
@@ -853,9 +857,12 @@ __device__ __forceinline__ void l2l_mfma32_body(const DevGeom &g, int nd, int L,
     cd acc = own ? loc[base] : mk(0.0, 0.0);
     f4 yr = {0.f, 0.f, 0.f, 0.f}, yi = {0.f, 0.f, 0.f, 0.f};
     int kb0, kb1;
-    ksplit(NKp, L2L_KS, w, &kb0, &kb1);
-    trans_block32(g.l2l_mf32 + g.l2l_mf_off[(L - 1) * 4 + t.q] + (long long)rb * NKp * 64, kb0, kb1, bptr,
-                  np, lane, yr, yi);
+    // the parts are those of the whole row: single-precision partial sums of
+    // other parts would round differently
+    ksplit(0, (np + 3) / 4, L2L_KS, w, &kb0, &kb1);
+    kb0 = max(kb0, rk.k0);
+    kb1 = min(kb1, rk.k1);
+    trans_block32(g.l2l_mf32 + ((long long)rk.off - rk.k0) * 64, kb0, kb1, bs, valid, np, lane, yr, yi);
 #pragma unroll
     for (int i = 0; i < 4; ++i) { part[w][lane][i] = (double)yr[i]; part[w][lane][4 + i] = (double)yi[i]; }
     __syncthreads();

@@ -20,6 +20,17 @@ namespace qbx {
 #define QBX_G
 #endif
 
+// One 16-row block of a translation table: its 16x4 blocks [k0, k1) follow
+// each other from block `off` of the table on.  The blocks outside hold only
+// terms below kTableDrop of their row's largest and are neither stored nor
+// multiplied (KeptRows in planner.hpp).  Measured, whole tables to kept
+// blocks: 32768-node star, one density, M2L 99.5 to 78.7 us, M2M 104 to 68,
+// L2L 93 to 81; four densities M2L 464 to 379, M2M 192 to 118, L2L 269 to
+// 214; 32 curves of 512-16384 nodes, four densities, 6.63 to 5.35 ms in all.
+struct RowBlk {
+    int off, k0, k1, pad;
+};
+
 // All pointers are device pointers.  Points are in tree (Morton) order.
 struct DevGeom {
     int ns, nc, nt, nb, nlev, p, n_smooth;
@@ -67,9 +78,11 @@ struct DevGeom {
     const QBX_G double *Wtab, *invW, *logW;
     const QBX_G long long *box_off;                  // per box, in coefficients of one density
     // M2M / L2L scaled matrices per (parent level, child quadrant) in MFMA
-    // A-operand order; child4[b*4+q] = child of b in quadrant q or -1
+    // A-operand order, the kept blocks of each row block only (RowBlk);
+    // child4[b*4+q] = child of b in quadrant q or -1
     const QBX_G cd *m2m_mf, *l2l_mf;
-    const QBX_G long long *m2m_mf_off, *l2l_mf_off;  // [level*4+q]
+    const QBX_G RowBlk *rblk;                        // row blocks of every table
+    const QBX_G int *m2m_rb0, *l2l_rb0;              // [level*4+q]: first row block
     const QBX_G int *child4;
     // per position of the M2M parent list: children's box_off by quadrant
     // (-1 = none) and the parent's; per position of the L2L child list: the
@@ -85,7 +98,7 @@ struct DevGeom {
     // tile order and offsets as the FP64 ones; null when off
     int far32;
     const QBX_G cf *m2l_mf32, *l2l_mf32;
-    const QBX_G long long *m2l_mf_off;               // [level*40+o]
+    const QBX_G int *m2l_rb0;                        // [level*40+o]: first row block
     const QBX_G int *vpair_sorted;                   // V-list positions sorted by (level, offset)
     const QBX_G long long *vy_off;                   // per V-list position: output row offset
     const QBX_G long long *m2l_src, *m2l_dst;        // per sorted position: box_off of the source, vy_off

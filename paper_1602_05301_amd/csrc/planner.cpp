@@ -183,7 +183,7 @@ std::vector<std::complex<long double>> outgoing_ld(double omega, double zx, doub
 
 }  // namespace
 
-std::vector<std::complex<double>> m2m_matrix(const Plan &pl, int l, int q)
+std::vector<std::complex<double>> m2m_matrix(const Plan &pl, int l, int q, const KeptRows &kr)
 {
     // a_n(parent) = sum_k a_k(child) I_{k-n}(m_p - m_c)        (Stage 2)
     int Pp = pl.P[l], Pc = pl.P[l + 1];
@@ -196,14 +196,14 @@ std::vector<std::complex<double>> m2m_matrix(const Plan &pl, int l, int q)
     int np = 2 * Pp + 1, nc = 2 * Pc + 1;
     std::vector<std::complex<double>> T((size_t)np * nc);
     for (int j = -Pp; j <= Pp; ++j)
-        for (int k = -Pc; k <= Pc; ++k) {
+        for (int k = kr.lo[j + Pp] - Pc; k <= kr.hi[j + Pp] - Pc; ++k) {
             std::complex<long double> v = I[k - j + N] * (Wc[std::abs(k)] / Wp[std::abs(j)]);
             T[(size_t)(j + Pp) * nc + (k + Pc)] = std::complex<double>((double)v.real(), (double)v.imag());
         }
     return T;
 }
 
-std::vector<std::complex<double>> l2l_matrix(const Plan &pl, int l, int q)
+std::vector<std::complex<double>> l2l_matrix(const Plan &pl, int l, int q, const KeptRows &kr)
 {
     // g'_j = sum_k g_k I_{j-k}(m_p - m_c)                        (Stage 7)
     int Pp = pl.P[l], Pc = pl.P[l + 1];
@@ -216,14 +216,14 @@ std::vector<std::complex<double>> l2l_matrix(const Plan &pl, int l, int q)
     int np = 2 * Pp + 1, nc = 2 * Pc + 1;
     std::vector<std::complex<double>> T((size_t)nc * np);
     for (int j = -Pc; j <= Pc; ++j)
-        for (int k = -Pp; k <= Pp; ++k) {
+        for (int k = kr.lo[j + Pc] - Pp; k <= kr.hi[j + Pc] - Pp; ++k) {
             std::complex<long double> v = I[j - k + N] * (Wc[std::abs(j)] / Wp[std::abs(k)]);
             T[(size_t)(j + Pc) * np + (k + Pp)] = std::complex<double>((double)v.real(), (double)v.imag());
         }
     return T;
 }
 
-std::vector<std::complex<double>> m2l_matrix(const Plan &pl, int l, int dx, int dy)
+std::vector<std::complex<double>> m2l_matrix(const Plan &pl, int l, int dx, int dy, const KeptRows &kr)
 {
     // g_j = (-1)^j sum_k a_k O_{k+j}(c - m)                      (Stage 4)
     int P = pl.P[l];
@@ -235,12 +235,153 @@ std::vector<std::complex<double>> m2l_matrix(const Plan &pl, int l, int dx, int 
     std::vector<std::complex<double>> T((size_t)n * n);
     for (int j = -P; j <= P; ++j) {
         long double sg = (j & 1) ? -1.0L : 1.0L;
-        for (int k = -P; k <= P; ++k) {
+        for (int k = kr.lo[j + P] - P; k <= kr.hi[j + P] - P; ++k) {
             std::complex<long double> v = O[k + j + N] * (sg * W[std::abs(j)] * W[std::abs(k)]);
             T[(size_t)(j + P) * n + (k + P)] = std::complex<double>((double)v.real(), (double)v.imag());
         }
     }
     return T;
+}
+
+namespace {
+
+constexpr double kLogZero = -1e30;
+
+double log_abs(long double v) { return v != 0.0L ? (double)std::log(std::fabs(v)) : kLogZero; }
+
+std::vector<double> log_j(double x, int N)
+{
+    std::vector<double> out(N + 1);
+    for (int n = 0; n <= N; ++n) out[n] = log_abs(jnl(n, (long double)x));
+    return out;
+}
+
+// log|H_n(x)|, n = 0..N (upward recurrence of ratio pairs, no overflow)
+std::vector<double> log_h(double x, int N)
+{
+    std::vector<double> out(N + 1);
+    std::complex<double> a(j0(x), y0(x)), b(j1(x), y1(x));
+    double shift = 0.0;
+    for (int n = 0; n <= N; ++n) {
+        out[n] = 0.5 * std::log(a.real() * a.real() + a.imag() * a.imag()) + shift;
+        std::complex<double> c = (2.0 * (n + 1) / x) * b - a;
+        a = b;
+        b = c;
+        if (std::fabs(b.imag()) > 1e100) {     // squares stay in range
+            a *= 1e-100;
+            b *= 1e-100;
+            shift += 100.0 * std::log(10.0);
+        }
+    }
+    return out;
+}
+
+// Input profiles: log-magnitudes of the coefficients by |k|, for a charge and
+// for a dipole (whose coefficients are the neighbouring orders').
+typedef std::vector<std::vector<double>> Profiles;
+
+void add_profiles(Profiles &pr, const std::vector<double> &mono)   // one order more than used
+{
+    int N = (int)mono.size() - 2;
+    pr.emplace_back(mono.begin(), mono.end() - 1);
+    std::vector<double> dip(N + 1);
+    for (int k = 0; k <= N; ++k) dip[k] = std::max(mono[k ? k - 1 : 1], mono[k + 1]);
+    pr.push_back(dip);
+}
+
+// |J_k| of a source at fractions of the box's half diagonal (its bound
+// min(1, (x/2)^k / k!)).
+Profiles multipole_profiles(double omega, double R, int P)
+{
+    Profiles pr;
+    for (double rho : {1.0, 0.5, 0.2, 0.05, 0.01, 1e-4}) {
+        std::vector<double> v(P + 2);
+        double ls = std::log(omega * R * rho / std::sqrt(2.0));
+        for (int k = 0; k <= P + 1; ++k) v[k] = std::min(0.0, k * ls - std::lgamma(k + 1.0));
+        add_profiles(pr, v);
+    }
+    return pr;
+}
+
+// |H_k| of a source from the nearest distance of a V- or X-list source on to
+// where every order counts alike.
+Profiles local_profiles(double omega, double R, int P)
+{
+    Profiles pr;
+    double x0 = 3.0 * omega * R;
+    for (double f : {1.0, 1.5, 2.5, 6.0, 20.0}) add_profiles(pr, log_h(f * x0, P + 1));
+    for (double x : {1.0, 10.0, 4.0 * P})
+        if (x > x0) add_profiles(pr, log_h(x, P + 1));
+    return pr;
+}
+
+// Rows -Pout..Pout with terms radial[|j - k|] (sum: |j + k|) times the
+// profile's |k|.  The bounds move by about one input per row, so every fourth
+// row is tested and the rows between take the wider bounds of the two beside
+// them; the row of order -j mirrors that of j.
+KeptRows kept_rows(int Pout, int Pin, bool sum, const std::vector<double> &radial, const Profiles &prof)
+{
+    const double drop = std::log(kTableDrop);
+    const int nin = 2 * Pin + 1, step = 4;
+    int nout = 2 * Pout + 1;
+    KeptRows kr{std::vector<int32_t>(nout), std::vector<int32_t>(nout)};
+    std::vector<double> base(nin);
+    for (int j = 0;; j = std::min(j + step, Pout)) {
+        for (int i = 0; i < nin; ++i) base[i] = radial[std::abs(sum ? j + i - Pin : j - i + Pin)];
+        int lo = nin - 1, hi = 0;
+        for (const auto &pf : prof) {
+            auto term = [&](int i) { return base[i] + pf[std::abs(i - Pin)]; };
+            double top = kLogZero;
+            for (int i = 0; i < nin; ++i) top = std::max(top, term(i));
+            double lim = top + drop;
+            for (int i = 0; i < lo; ++i)
+                if (!(term(i) <= lim)) { lo = i; break; }
+            for (int i = nin - 1; i > hi; --i)
+                if (!(term(i) <= lim)) { hi = i; break; }
+        }
+        kr.lo[Pout + j] = std::min(lo, hi);
+        kr.hi[Pout + j] = std::max(lo, hi);
+        if (j == Pout) break;
+    }
+    for (int j0 = 0; j0 < Pout; j0 += step) {
+        int j1 = std::min(j0 + step, Pout);
+        for (int j = j0 + 1; j < j1; ++j) {
+            kr.lo[Pout + j] = std::min(kr.lo[Pout + j0], kr.lo[Pout + j1]);
+            kr.hi[Pout + j] = std::max(kr.hi[Pout + j0], kr.hi[Pout + j1]);
+        }
+    }
+    for (int j = 1; j <= Pout; ++j) {
+        kr.lo[Pout - j] = nin - 1 - kr.hi[Pout + j];
+        kr.hi[Pout - j] = nin - 1 - kr.lo[Pout + j];
+    }
+    return kr;
+}
+
+}  // namespace
+
+KeptRows m2m_kept(const Plan &pl, int l)
+{
+    int Pp = pl.P[l], Pc = pl.P[l + 1];
+    double Rc = pl.box_radius(l + 1);
+    return kept_rows(Pp, Pc, false, log_j(pl.omega * Rc * std::sqrt(2.0), Pp + Pc),
+                     multipole_profiles(pl.omega, Rc, Pc));
+}
+
+KeptRows l2l_kept(const Plan &pl, int l)
+{
+    int Pp = pl.P[l], Pc = pl.P[l + 1];
+    return kept_rows(Pc, Pp, false, log_j(pl.omega * pl.box_radius(l + 1) * std::sqrt(2.0), Pp + Pc),
+                     local_profiles(pl.omega, pl.box_radius(l), Pp));
+}
+
+std::vector<KeptRows> m2l_kept(const Plan &pl, int l, const std::vector<int> &dist2)
+{
+    int P = pl.P[l];
+    double R = pl.box_radius(l);
+    Profiles pr = multipole_profiles(pl.omega, R, P);
+    std::vector<KeptRows> out;
+    for (int d2 : dist2) out.push_back(kept_rows(P, P, true, log_h(2.0 * pl.omega * R * std::sqrt((double)d2), 2 * P), pr));
+    return out;
 }
 
 namespace {

@@ -73,12 +73,36 @@ int fmm_order(double omega, double R, double eps);
 // k = 0..P_l.  Multipoles are stored as a_k / W_|k| and locals as g_k W_|k|.
 std::vector<double> level_scales(double omega, double R, int P);
 
-// Scaled translation matrices (row-major [out][in], complex<double>).
+// Which entries of a translation's rows count: row j (order j - P_out) takes
+// its inputs [lo[j], hi[j]] (indices into the P_in orders); all others add less
+// than kTableDrop of the row's largest term, whatever the sources.
+//
+// Where a box is small against the wavelength the translations couple orders
+// of one sign only (M2M: |k| up to the row's |j| and a few beyond; L2L: from
+// it on; M2L: both, thinning out towards k = -j); the rest falls off like
+// powers of (omega R)^2.  The test is on the terms themselves, radial factor
+// times input coefficient, unscaled, since what a row adds up depends on how
+// its inputs fall off: multipole coefficients of a charge or dipole at any
+// distance from the box centre up to its corner, local coefficients of one at
+// any distance from three box radii on.  For each such profile the dropped
+// terms (at most 2 P + 1) are below 1e-17 of the row's largest, where its own
+// rounding is 1e-16.  32768-node star, orders 63: 0.6 of M2L's 16x4 blocks
+// are kept, 0.4 of M2M's and 0.5 of L2L's.
+constexpr double kTableDrop = 1e-20;
+struct KeptRows {
+    std::vector<int32_t> lo, hi;
+};
+KeptRows m2m_kept(const Plan &pl, int l);                          // any child quadrant
+KeptRows l2l_kept(const Plan &pl, int l);
+std::vector<KeptRows> m2l_kept(const Plan &pl, int l, const std::vector<int> &dist2);   // |offset|^2 in box sides
+
+// Scaled translation matrices (row-major [out][in], complex<double>), zero
+// outside the kept entries.
 // M2M: child (level l+1, quadrant q) -> parent (level l).
-std::vector<std::complex<double>> m2m_matrix(const Plan &pl, int l, int quadrant);
+std::vector<std::complex<double>> m2m_matrix(const Plan &pl, int l, int quadrant, const KeptRows &kr);
 // L2L: parent (level l) -> child (level l+1, quadrant q).
-std::vector<std::complex<double>> l2l_matrix(const Plan &pl, int l, int quadrant);
+std::vector<std::complex<double>> l2l_matrix(const Plan &pl, int l, int quadrant, const KeptRows &kr);
 // M2L at level l for source box offset (dx, dy) (in box sides) from the target box.
-std::vector<std::complex<double>> m2l_matrix(const Plan &pl, int l, int dx, int dy);
+std::vector<std::complex<double>> m2l_matrix(const Plan &pl, int l, int dx, int dy, const KeptRows &kr);
 
 }  // namespace qbx

@@ -1,0 +1,49 @@
+"""Kernels at the sizes where their splits and ranges can go wrong, through
+the C ABI against the FP64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1602_05301_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1602_05301_amd import qbx
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return qbx.Context(0)
+
+
+def _dev(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _densities(g, nd, seed):
+    r = inputs.rng_for(seed, inputs.PURPOSE_DENSITY)
+    return inputs.complex_gaussian(r, (nd, g.n)), inputs.complex_gaussian(r, (nd, g.n))
+
+
+# Translation tables hold only the entries that count for a row.  With the
+# order increment far above what eps needs, truncation is below rounding, and
+# what is left is rounding (1e-13 at these orders) and whatever the dropped
+# entries add: 1e-12 for both.  The frequencies take boxes from far below the
+# wavelength (scale factors at their lower clamp; at much lower frequencies
+# still, such orders overflow) to several wavelengths.
+@pytest.mark.parametrize("which", ["S", "D"])
+@pytest.mark.parametrize("omega", [2.0, 20.0, 150.0])
+def test_translation_rows_keep_what_counts(ctx, omega, which):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(80, 16, lobes=5, amp=0.3)
+    p = 8
+    s, _ = _densities(g, 1, 40)
+    ss, sd = (s, None) if which == "S" else (None, s)
+    tc = np.arange(g.n, dtype=np.int32)
+    ref = oracle.direct_qbx(omega, p, g, g.sx, g.sy, ss, sd, tgt_ctr=tc)
+    geo = qbx.Geometry(ctx, g, omega, 1e-13, g.sx, g.sy, tc, qbx.options(p=p, p_add=70, leaf_max=24))
+    u = geo.eval(_dev(ss), _dev(sd)).cpu().numpy()
+    err = np.linalg.norm(u - ref) / np.linalg.norm(ref)
+    print(f"omega {omega} {which}: {err:.2e}", flush=True)
+    assert err <= 1e-12
