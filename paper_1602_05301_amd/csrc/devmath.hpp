@@ -1,14 +1,15 @@
 // Complex arithmetic and Bessel/Hankel sequences for the gfx950 kernels.
 //
 // Hankel functions H_n^{(1)}(x) = J_n(x) + i Y_n(x) of real argument: H_0 and
-// H_1 from their ascending series for x <= 4 and from the HIP device math
-// library (j0, y0, j1, y1) above, higher orders by the
+// H_1 from polynomial fits in two ranges (hankel01), higher orders by the
 // upward three-term recurrence H_{n+1} = (2n/x) H_n - H_{n-1}, which is
 // stable because Y_n dominates.  J_n by Miller's backward recurrence,
 // normalised against whichever of J_0(x), J_1(x) is larger in magnitude.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include "hankelcoef.hpp"
 
 namespace qbx {
 
@@ -85,7 +86,7 @@ __device__ inline void besselj_seq(double x, int N, double *out, long long strid
     for (int n = M; n > 0; --n) {
         if (n <= N) out[n * stride] = f;
         if (n == 1) f1 = f;
-        double fm = (n * inv) * f - fp1;
+        double fm = fma(n * inv, f, -fp1);
         fp1 = f;
         f = fm;
         if (fabs(f) > 1e250) {
@@ -101,56 +102,185 @@ __device__ inline void besselj_seq(double x, int N, double *out, long long strid
     for (int n = 1; n <= N; ++n) out[n * stride] *= s;
 }
 
-__device__ __attribute__((noinline)) void hankel01_lib(double x, cd &h0, cd &h1)
+// 1/sqrt(d) to about an ulp: the hardware estimate and one third-order step.
+__device__ __forceinline__ double fast_rsqrt(double d)
 {
-    h0 = mk(j0(x), y0(x));
-    h1 = mk(j1(x), y1(x));
+    double y = __builtin_amdgcn_rsq(d);
+    double e = fma(-(d * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-constexpr double kSeriesMaxX = 4.0;
-
-// J0, J1, Y0, Y1 for 0 < x <= kSeriesMaxX from their ascending series
-// (DLMF 10.2.2 and 10.8.1), t = x^2/4, H_k the harmonic numbers:
-//   J0 = sum_k (-t)^k/(k!)^2,           J1 = (x/2) sum_k (-t)^k/(k!(k+1)!)
-//   Y0 = (2/pi)[(ln(x/2) + gamma) J0 - sum_k H_k (-t)^k/(k!)^2]
-//   Y1 = -2/(pi x) + (2/pi)(ln(x/2) + gamma) J1
-//        - (x/(2 pi)) sum_k (H_k + H_{k+1}) (-t)^k/(k!(k+1)!)
-// Terms up to k = 18: at x = 4 the first omitted one is below 1e-22 (the
-// error against SciPy over (0, 4] is the same as with more terms, about
-// 2e-15 of |H|, all rounding); the largest term is 4, so at most a few ulps
-// are lost to cancellation.
-__device__ __forceinline__ void hankel01_series(double x, cd &h0, cd &h1)
+// r = sqrt(r2) and 1/r: one estimate for both where r2 is far from the ends of
+// the range, the plain operations there.
+__device__ __forceinline__ void dist_and_inverse(double r2, double &r, double &ir)
 {
-    const double t = -0.25 * x * x;
-    double c = 1.0, d = 1.0;                      // (-t)^k/(k!)^2, (-t)^k/(k!(k+1)!)
-    double sj0 = 1.0, sj1 = 1.0, sy0 = 0.0, sy1 = 1.0;
-    double Hk = 0.0;
-#pragma unroll
-    for (int k = 1; k <= 18; ++k) {
-        c *= t * (1.0 / ((double)k * k));
-        d *= t * (1.0 / ((double)k * (k + 1)));
-        Hk += 1.0 / k;
-        double Hk1 = Hk + 1.0 / (k + 1);
-        sj0 += c;
-        sj1 += d;
-        sy0 = fma(Hk, c, sy0);
-        sy1 = fma(Hk + Hk1, d, sy1);
+    if (r2 > 1e-290 && r2 < 1e290) {
+        ir = fast_rsqrt(r2);
+        double r0 = r2 * ir;
+        r = fma(fma(-r0, r0, r2), 0.5 * ir, r0);
+        ir = fma(ir, fma(-r, ir, 1.0), ir);
+    } else {
+        r = sqrt(r2);
+        ir = 1.0 / r;
     }
-    const double two_pi = 0.63661977236758134308;       // 2/pi
-    const double euler_gamma = 0.57721566490153286061;
-    double L = log(0.5 * x) + euler_gamma;
-    double J0 = sj0, J1 = 0.5 * x * sj1;
-    double Y0 = two_pi * (L * J0 - sy0);
-    double Y1 = -two_pi / x + two_pi * L * J1 - (0.5 / 3.14159265358979323846) * x * sy1;
-    h0 = mk(J0, Y0);
-    h1 = mk(J1, Y1);
 }
 
-__device__ __forceinline__ void hankel01(double x, cd &h0, cd &h1)
+// 1/x from an estimate a few ulps off (orders up to 40 raise its error to
+// their power).
+__device__ __forceinline__ double refine_inverse(double x, double est)
 {
-    if (x <= kSeriesMaxX) hankel01_series(x, h0, h1);
-    else hankel01_lib(x, h0, h1);
+    double e = fma(-x, est, 1.0);
+    return fabs(e) < 0.5 ? fma(est, e, est) : est;    // 0, infinity stay
 }
+
+// Coefficient tables are read through the constant address space, as scalar
+// loads, and the polynomial steps take them as scalar operands: a
+// double-precision instruction has no 64-bit literal, and the compiler's own
+// choice (constants moved into vector registers, the rest spilled) costs two
+// moves a step.  coef_after gives an opaque pointer that is there only once
+// `v` is, so that a loop neither keeps a hundred coefficients in registers
+// nor loads them all ahead.
+#ifdef __HIP_DEVICE_COMPILE__
+typedef const __attribute__((address_space(4))) double *CoefPtr;
+__device__ __forceinline__ CoefPtr coef_after(const double *t, double v)
+{
+    CoefPtr c = (CoefPtr)t;
+    asm volatile("" : "+s"(c) : "v"(v));
+    return c;
+}
+__device__ __forceinline__ double fma_s(double a, double b, double c)
+{
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+}
+#else
+typedef const double *CoefPtr;
+__device__ __forceinline__ CoefPtr coef_after(const double *t, double) { return t; }
+__device__ __forceinline__ double fma_s(double a, double b, double c) { return fma(a, b, c); }
+#endif
+
+// Four polynomials of ROWS coefficients each (in turn, highest first) at s.
+// The coefficients of two rows are one load, two loads ahead of their use.
+template <int ROWS>
+__device__ __forceinline__ void poly4(const double *t, double s, double (&p)[4])
+{
+    static_assert(ROWS % 2 == 0, "rows are loaded in pairs");
+    constexpr int G = ROWS / 2, AHEAD = 2;
+    double c[G][8];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if (g < AHEAD) {
+            CoefPtr q = coef_after(t + 8 * g, s);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) c[g][i] = q[i];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if (g + AHEAD < G) {
+            CoefPtr q = coef_after(t + 8 * (g + AHEAD), g ? p[0] : s);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) c[g + AHEAD][i] = q[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = g ? fma_s(p[i], s, c[g][i]) : c[g][i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = fma_s(p[i], s, c[g][4 + i]);
+    }
+}
+
+// (1/pi) ln z, z > 0: z = 2^e m, m in [sqrt(1/2), sqrt(2)),
+// ln m = 2 atanh((m - 1)/(m + 1)).
+__device__ __forceinline__ double log_over_pi(double z)
+{
+    double m = __builtin_amdgcn_frexp_mant(z);
+    int e = __builtin_amdgcn_frexp_exp(z);
+    bool low = m < 0.70710678118654752;
+    m = low ? m + m : m;
+    e -= low;
+    double num = m - 1.0, den = m + 1.0;
+    double r = __builtin_amdgcn_rcp(den);
+    r = fma(fma(-den, r, 1.0), r, r);
+    double t = num * r;
+    t = fma(fma(-t, den, num), r, t);
+    double t2 = t * t;
+    CoefPtr c = coef_after(kLogPoly, t2);
+    double q = c[7];
+#pragma unroll
+    for (int k = 6; k >= 0; --k) q = fma_s(q, t2, c[k]);
+    double lm = fma(t * t2, q, t);
+    // ln 2 / pi in two parts, 2/pi times the rest
+    double de = (double)e;
+    return fma(de, 0.2206356001526516, fma(de, -7.461721539413406e-18, 0.63661977236758134308 * lm));
+}
+
+// sin x and cos x, x >= 0.  Up to 1e9 the reduction by multiples of pi/2 in
+// two parts is exact to rounding; beyond, the library's.
+__device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
+{
+    if (x > 1e9) {
+        sincos(x, &s, &c);
+        return;
+    }
+    double k = rint(x * 0.63661977236758134308);
+    double r = fma(-k, 1.5707963267948965580, x);
+    r = fma(-k, 6.1232339957367658860e-17, r);
+    double z = r * r;
+    CoefPtr p = coef_after(kSinCosPoly, z);
+    double a = p[10], b = p[11];
+#pragma unroll
+    for (int i = 4; i >= 0; --i) {
+        a = fma_s(a, z, p[2 * i]);
+        b = fma_s(b, z, p[2 * i + 1]);
+    }
+    double sr = fma(r * z, a, r), cr = fma(z * z, b, fma(z, -0.5, 1.0));
+    int q = (int)k;
+    double u = (q & 1) ? cr : sr, v = (q & 1) ? sr : cr;
+    s = (q & 2) ? -u : u;
+    c = ((q + 1) & 2) ? -v : v;
+}
+
+// H_0(x) and H_1(x), x > 0, with ix = 1/x, in two ranges: up to 4 polynomials
+// in x^2 beside the logarithm (about 90 double-precision instructions), above
+// it modulus-and-phase form with polynomials in 1/x^2 (about 130); see
+// hankelcoef.hpp.  Measured per wave (64 arguments, 1/x included): 670 cycles
+// of a SIMD up to 4 and 1000 above, against 1450-1750 for the ascending series
+// and 3500 for the device library's j0, y0, j1, y1; a wave with both, 1050.
+// The error is that of those within rounding: 1e-16 of |H_n| on average, 5e-16
+// at most, and 3e-16 and 1.3e-15 between 2 and 4 (9000 arguments, 1e-6 to 3000,
+// against 30-digit values).  A lower bound makes the upper range's polynomials longer, a
+// higher one costs the lower range its last bits (at 6, 3e-16 of |H| against
+// the 1e-16 of the upper form).
+constexpr double kHankelSmallX = 4.0;
+
+__device__ __forceinline__ void hankel01(double x, double ix, cd &h0, cd &h1)
+{
+    const double two_over_pi = 0.63661977236758134308;
+    double p[4];
+    if (x <= kHankelSmallX) {
+        double t = x * x;
+        poly4<kHankelSmallRows>(kHankelSmall, fma(t, 0.125, -1.0), p);
+        // (2/pi) (ln(x/2) + gamma) = (1/pi) ln(x^2 e^{2 gamma} / 4)
+        double L = log_over_pi(t * 0.79305473953136263);
+        double j0 = fma(t, p[0], 1.0), j1 = x * fma(t, p[2], 0.5);
+        h0 = mk(j0, fma(L, j0, t * p[1]));
+        h1 = mk(j1, fma(-two_over_pi, ix, fma(L, j1, x * fma(t, p[3], -0.15915494309189533577))));
+        return;
+    }
+    poly4<kHankelLargeRows>(kHankelLarge, fma(ix * ix, 32.0, -1.0), p);
+    double sn, cs;
+    fast_sincos(x, sn, cs);
+    // e = sqrt(2/(pi x)) e^{i (x - pi/4)}; H_1 has a further -i
+    double f = fast_rsqrt(3.14159265358979323846 * x);
+    if (x > 1e300) f = 0.0, sn = cs = 0.0;
+    cd e = mk(f * (cs + sn), f * (sn - cs));
+    double q0 = p[1] * ix, q1 = p[3] * ix;
+    h0 = mk(fma(p[0], e.x, fma(-q0, e.y, e.x)), fma(p[0], e.y, fma(q0, e.x, e.y)));
+    h1 = mk(fma(p[2], e.y, fma(q1, e.x, e.y)), -fma(p[2], e.x, fma(-q1, e.y, e.x)));
+}
+
+__device__ __forceinline__ void hankel01(double x, cd &h0, cd &h1) { hankel01(x, 1.0 / x, h0, h1); }
 
 // A_n = tau^n H_n(x), n = 0..N, written to out[n * stride].  With
 // tau = min(1, x/2) the sequence stays below (n-1)! in magnitude.
@@ -164,7 +294,8 @@ __device__ inline void scaled_hankel_seq(double x, double tau, int N, cd *out, l
     double t2 = tau * tau;
     double c = 2.0 * tau / x;                 // one division, outside the recurrence
     for (int n = 1; n < N; ++n) {
-        cd a2 = (((double)n * c) * a1) - (t2 * a0);
+        double nc = (double)n * c;
+        cd a2 = mk(fma(nc, a1.x, -(t2 * a0.x)), fma(nc, a1.y, -(t2 * a0.y)));
         out[(n + 1) * stride] = a2;
         a0 = a1;
         a1 = a2;

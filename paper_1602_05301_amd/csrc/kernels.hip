@@ -1163,20 +1163,20 @@ __global__ void __launch_bounds__(64) k_p2l_xc_capped(DevGeom g, int n, const in
 // so only H_0..H_p are needed.
 // ---------------------------------------------------------------------------
 template <int PB>
-__device__ __forceinline__ void p2qbxl_pair(double omega, int p, double cx, double cy, double sx,
+__device__ __forceinline__ void p2qbxl_pair(double omega, double iomega, double cx, double cy, double sx,
                                             double sy, double nx, double ny, cd qS, cd qD, cd *acc)
 {
     double dx = sx - cx, dy = sy - cy;
-    double r = sqrt(dx * dx + dy * dy);
-    double x = omega * r;
-    double ir = 1.0 / r;
+    double r, ir;
+    dist_and_inverse(dx * dx + dy * dy, r, ir);
+    double x = omega * r, ix = refine_inverse(x, iomega * ir);
     cd u = mk(dx * ir, dy * ir);
     cd H0, H1;
-    hankel01(x, H0, H1);
+    hankel01(x, ix, H0, H1);
     cd c = (0.5 * omega) * qD;
     cd v = mk(nx, ny) * conj(u);
     cd A = (2.0 * v.x) * c;
-    double ix2 = 2.0 / x;
+    double ix2 = 2.0 * ix;
     cd B = ix2 * (c * conj(v));
     cd Bp = ix2 * (c * v);
     {
@@ -1200,7 +1200,8 @@ __device__ __forceinline__ void p2qbxl_pair(double omega, int p, double cx, doub
             cp = cp - B;
             cm = cm - Bp;
             up = up * u;
-            cd Hn = (((double)m * ix2) * Hcur) - Hprev;
+            double mx = (double)m * ix2;
+            cd Hn = mk(fma(mx, Hcur.x, -Hprev.x), fma(mx, Hcur.y, -Hprev.y));
             Hprev = Hcur;
             Hcur = Hn;
         }
@@ -1270,6 +1271,7 @@ __device__ __forceinline__ void p2qbxl_body(const DevGeom &g, int nd, const int 
     int tid = threadIdx.x;
     int gi = tid % CG, part = tid / CG;
     int p = g.p;
+    double iomega = 1.0 / g.omega;
     long long ncoef = 2 * p + 1;
     for (int cg = c0; cg < c1; cg += CG) {
         int i = cg + gi, ncg = min(CG, c1 - cg);
@@ -1295,7 +1297,7 @@ __device__ __forceinline__ void p2qbxl_body(const DevGeom &g, int nd, const int 
                 if (active) {
 #pragma unroll 1
                     for (int f = part; f < cnt; f += parts)
-                        p2qbxl_pair<PB>(g.omega, p, cx, cy, SX[f], SY[f], NX[f], NY[f], QS[f], QD[f], acc);
+                        p2qbxl_pair<PB>(g.omega, iomega, cx, cy, SX[f], SY[f], NX[f], NY[f], QS[f], QD[f], acc);
                 }
             }
             // sum the parts of each centre in part order
@@ -1351,6 +1353,7 @@ __device__ __forceinline__ void p2qbxl_direct_body(const DevGeom &g, int nd, int
     int i = bid.x * G + gi;
     bool active = i < g.nc;
     int p = g.p;
+    double iomega = 1.0 / g.omega;
     long long ncoef = 2 * p + 1;
     double cx = active ? g.cx[i] : 0.0, cy = active ? g.cy[i] : 0.0;
     for (int d = 0; d < nd; ++d) {
@@ -1360,7 +1363,7 @@ __device__ __forceinline__ void p2qbxl_direct_body(const DevGeom &g, int nd, int
         if (active)
 #pragma unroll 1
             for (int j = part; j < g.ns; j += parts)
-                p2qbxl_pair<PB>(g.omega, p, cx, cy, g.sx[j], g.sy[j], g.snx[j], g.sny[j],
+                p2qbxl_pair<PB>(g.omega, iomega, cx, cy, g.sx[j], g.sy[j], g.snx[j], g.sny[j],
                                 qs[(long long)d * g.ns + j], qd[(long long)d * g.ns + j], acc);
         p2qbxl_finish<PB>(acc, G, p, active && part == 0,
                           coef + (long long)d * ncoef * g.nc + (active ? i : 0), g.nc, false);
@@ -1834,7 +1837,7 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
                 ep = ep * v;
             }
             if (n == 1) f1 = f;
-            double fm = (n * inv) * f - fp1;
+            double fm = fma(n * inv, f, -fp1);
             fp1 = f;
             f = fm;
             if (fabs(f) > 1e250) {
@@ -1865,7 +1868,7 @@ __device__ __forceinline__ void smooth_body(const DevGeom &g, int nd, const cd *
     if (idx >= g.n_smooth) return;                    // uniform across the wave
     int lane = threadIdx.x;
     int m = g.smooth_list[idx];
-    double tx = g.tx[m], ty = g.ty[m];
+    double tx = g.tx[m], ty = g.ty[m], iomega = 1.0 / g.omega;
     for (int d0 = 0; d0 < nd; d0 += SMOOTH_ND) {
         int dn = min(SMOOTH_ND, nd - d0);
         cd acc[SMOOTH_ND];
@@ -1873,11 +1876,11 @@ __device__ __forceinline__ void smooth_body(const DevGeom &g, int nd, const cd *
         for (int e = 0; e < SMOOTH_ND; ++e) acc[e] = mk(0.0, 0.0);
         for (int j = lane; j < g.ns; j += 64) {
             double dx = tx - g.sx[j], dy = ty - g.sy[j];
-            double r = sqrt(dx * dx + dy * dy);
-            double x = g.omega * r;
+            double r, ir;
+            dist_and_inverse(dx * dx + dy * dy, r, ir);
             cd h0, h1;
-            hankel01(x, h0, h1);
-            cd dh = (g.omega * (dx * g.snx[j] + dy * g.sny[j]) / r) * h1;
+            hankel01(g.omega * r, iomega * ir, h0, h1);
+            cd dh = (g.omega * (dx * g.snx[j] + dy * g.sny[j]) * ir) * h1;
 #pragma unroll
             for (int e = 0; e < SMOOTH_ND; ++e)
                 if (e < dn) {

@@ -47,3 +47,29 @@ def test_translation_rows_keep_what_counts(ctx, omega, which):
     err = np.linalg.norm(u - ref) / np.linalg.norm(ref)
     print(f"omega {omega} {which}: {err:.2e}", flush=True)
     assert err <= 1e-12
+
+
+# H_0 and H_1 on both sides of the bound between their two forms, close to
+# zero and at a few hundred wavelengths: one source at the
+# origin, p = 0, every target at its centre on the axis, so that each value is
+# (i/4) H_0(x) or (i/4) H_1(x) with x exact.  The fits are within 1.3e-15 of
+# |H|, and a few roundings follow: 4e-15.
+@pytest.mark.parametrize("which", ["S", "D"])
+def test_hankel_forms_meet(ctx, which):
+    mp = pytest.importorskip("mpmath")
+    from paper_1602_05301_amd import qbx
+    x = np.concatenate([2.0 ** np.arange(-40, 12, 3.0), np.nextafter(4.0, [0.0, 9.0]),
+                        np.linspace(0.5, 12.0, 93), np.linspace(100.0, 1000.0, 61)])
+    pts = inputs.Points(np.zeros(1), np.zeros(1), np.ones(1), np.ones(1), np.zeros(1), np.ones(1),
+                        x, 0.0 * x, 0.25 * x)
+    geo = qbx.Geometry(ctx, pts, 1.0, 1e-10, x, 0.0 * x, np.arange(x.size, dtype=np.int32),
+                       qbx.options(p=0, direct=True))
+    sig = _dev(np.ones((1, 1), dtype=np.complex128))
+    u = geo.eval(sig if which == "S" else None, sig if which == "D" else None).cpu().numpy()[0]
+    n = 0 if which == "S" else 1
+    with mp.workdps(40):
+        ref = np.array([complex(mp.mpc(0, 0.25) * (mp.besselj(n, mp.mpf(float(v))) + 1j * mp.bessely(n, mp.mpf(float(v)))))
+                        for v in x])
+    err = np.abs(u - ref) / np.abs(ref)
+    print(f"{which}: {err.max():.2e} at x = {x[err.argmax()]:g}", flush=True)
+    assert err.max() <= 4e-15
