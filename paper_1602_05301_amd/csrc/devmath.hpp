@@ -215,14 +215,10 @@ __device__ __forceinline__ double log_over_pi(double z)
     return fma(de, 0.2206356001526516, fma(de, -7.461721539413406e-18, 0.63661977236758134308 * lm));
 }
 
-// sin x and cos x, x >= 0.  Up to 1e9 the reduction by multiples of pi/2 in
-// two parts is exact to rounding; beyond, the library's.
+// sin x and cos x, 0 <= x <= 1e14: reduction by multiples k of pi/2 in two
+// parts, of which the first is exact and the second off by k 1e-33.
 __device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
 {
-    if (x > 1e9) {
-        sincos(x, &s, &c);
-        return;
-    }
     double k = rint(x * 0.63661977236758134308);
     double r = fma(-k, 1.5707963267948965580, x);
     r = fma(-k, 6.1232339957367658860e-17, r);
@@ -235,7 +231,7 @@ __device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
         b = fma_s(b, z, p[2 * i + 1]);
     }
     double sr = fma(r * z, a, r), cr = fma(z * z, b, fma(z, -0.5, 1.0));
-    int q = (int)k;
+    int q = (int)fma(-4.0, floor(0.25 * k), k);
     double u = (q & 1) ? cr : sr, v = (q & 1) ? sr : cr;
     s = (q & 2) ? -u : u;
     c = ((q + 1) & 2) ? -v : v;
@@ -273,7 +269,7 @@ __device__ __forceinline__ void hankel01(double x, double ix, cd &h0, cd &h1)
     fast_sincos(x, sn, cs);
     // e = sqrt(2/(pi x)) e^{i (x - pi/4)}; H_1 has a further -i
     double f = fast_rsqrt(3.14159265358979323846 * x);
-    if (x > 1e300) f = 0.0, sn = cs = 0.0;
+    if (x > 1e14) f = 0.0, sn = cs = 0.0;     // x has no phase left (plans end far below)
     cd e = mk(f * (cs + sn), f * (sn - cs));
     double q0 = p[1] * ix, q1 = p[3] * ix;
     h0 = mk(fma(p[0], e.x, fma(-q0, e.y, e.x)), fma(p[0], e.y, fma(q0, e.x, e.y)));

@@ -1153,15 +1153,26 @@ __global__ void __launch_bounds__(64) k_p2l_xc_capped(DevGeom g, int n, const in
 
 // ---------------------------------------------------------------------------
 // Stage 3: P2QBXL.  alpha_l(c) += qS O_l(s-c) + qD (w/2)(nu O_{l-1} - conj(nu) O_{l+1}).
-// With z = s - c = (x/omega) u, |u| = 1, O_{+-m} = (+-1)^m H_m u^{+-m} and the
-// recurrence H_{m+1} = (2m/x) H_m - H_{m-1}, the dipole pair folds into two
-// terms per order.  Writing c = (w/2) qD, v = nu conj(u), A = 2 Re(v) c,
-// B = (2/x) c conj(v), B' = (2/x) c v:
-//   alpha_0  += qS H_0 - A H_1,
-//   alpha_m  += u^m [(qS - m B) H_m + A H_{m-1}],
-//   alpha_-m += (-1)^m conj(u)^m [(qS - m B') H_m + A H_{m-1}],   m >= 1,
-// so only H_0..H_p are needed.
+// With z = s - c = (x/omega) u, |u| = 1, O_{+-m} = (+-1)^m H_m u^{+-m} and
+// c = (w/2) qD, v = nu conj(u), the recurrence H_{m+1} = (2m/x) H_m - H_{m-1}
+// takes H_{m+1} out of the dipole pair.  What is left needs the coefficient
+// times Hankel products only, Q_m = qS H_m and G_m = c H_m, which obey the same
+// recurrence, and real factors: with u^m = C + i S,
+//   T_m = Q_m + 2 Re(v) (G_{m-1} - (m/x) G_m),   k = (2m/x) Im(v),
+//   E_m = C T_m - S k G_m,   F_m = S T_m + C k G_m,
+//   alpha_m += E_m + i F_m,   alpha_-m += (-1)^m (E_m - i F_m),
+// 24 operations an order.  A lane sums E and F; alpha is formed from the
+// sums.  Bound by instruction issue: with the two orders' dipole factors as
+// complex coefficients of H_m an order took 33, and 3600 centres and sources
+// with two densities, p = 16, took 726 us directly, now 630 (6.6 cycles of a
+// SIMD an instruction at 2 waves; double-precision products run at 5, their
+// power-limited rate); near field of 110000 nodes in leaves of 64, p = 12,
+// 274 to 249 us; 200000 nodes in leaves of 32, p = 14, 374 to 349.  Measured
+// and dropped: the orders split over two waves with the pairs' Hankel values
+// shared through LDS, 4 waves a SIMD (direct 957 us, 200000 nodes 405 us: the
+// barriers and the second half's start cost more than the waves hide).
 // ---------------------------------------------------------------------------
+// Sums of a lane: E_m at acc[2m - 1], F_m at acc[2m], E_0 at acc[0].
 template <int PB>
 __device__ __forceinline__ void p2qbxl_pair(double omega, double iomega, double cx, double cy, double sx,
                                             double sy, double nx, double ny, cd qS, cd qD, cd *acc)
@@ -1175,37 +1186,48 @@ __device__ __forceinline__ void p2qbxl_pair(double omega, double iomega, double 
     hankel01(x, ix, H0, H1);
     cd c = (0.5 * omega) * qD;
     cd v = mk(nx, ny) * conj(u);
-    cd A = (2.0 * v.x) * c;
-    double ix2 = 2.0 * ix;
-    cd B = ix2 * (c * conj(v));
-    cd Bp = ix2 * (c * v);
-    {
-        cd t = qS * H0;
-        cfma(t, neg(A), H1);
-        acc[PB] = acc[PB] + t;
-    }
-    cd Hprev = H0, Hcur = H1;           // H_{m-1}, H_m
-    cd cp = qS - B, cm = qS - Bp;       // qS - m B, qS - m B'
+    double vr2 = 2.0 * v.x, vi2 = 2.0 * v.y;
+    cd Gp = c * H0, G = c * H1, Qp = qS * H0, Q = qS * H1;     // orders m - 1 and m
+    acc[0] = acc[0] + mk(fma(-vr2, G.x, Qp.x), fma(-vr2, G.y, Qp.y));
     cd up = u;                          // u^m
+    double mx = ix;                     // m / x
     // all PB orders, without branches; orders above p are discarded by the caller
 #pragma unroll
     for (int m = 1; m <= PB; ++m) {
-        cd AH = A * Hprev;
-        cd P = AH, M = AH;
-        cfma(P, cp, Hcur);
-        cfma(M, cm, Hcur);
-        cfma(acc[PB + m], up, P);
-        cfma(acc[PB - m], (m & 1) ? neg(conj(up)) : conj(up), M);
+        double k = mx * vi2, sk = up.y * k, ck = up.x * k;
+        cd t = mk(fma(-mx, G.x, Gp.x), fma(-mx, G.y, Gp.y));
+        cd T = mk(fma(vr2, t.x, Q.x), fma(vr2, t.y, Q.y));
+        cd &E = acc[2 * m - 1], &F = acc[2 * m];
+        E.x = fma(-sk, G.x, fma(up.x, T.x, E.x));
+        E.y = fma(-sk, G.y, fma(up.x, T.y, E.y));
+        F.x = fma(ck, G.x, fma(up.y, T.x, F.x));
+        F.y = fma(ck, G.y, fma(up.y, T.y, F.y));
         if (m < PB) {
-            cp = cp - B;
-            cm = cm - Bp;
+            double m2 = mx + mx;
+            cd Gn = mk(fma(m2, G.x, -Gp.x), fma(m2, G.y, -Gp.y));
+            cd Qn = mk(fma(m2, Q.x, -Qp.x), fma(m2, Q.y, -Qp.y));
+            Gp = G, G = Gn, Qp = Q, Q = Qn;
             up = up * u;
-            double mx = (double)m * ix2;
-            cd Hn = mk(fma(mx, Hcur.x, -Hprev.x), fma(mx, Hcur.y, -Hprev.y));
-            Hprev = Hcur;
-            Hcur = Hn;
+            mx = (double)(m + 1) * ix;
         }
     }
+}
+
+// alpha_-PB..alpha_PB from the sums E and F, in place (acc[PB + l]).
+template <int PB>
+__device__ __forceinline__ void p2qbxl_alpha(cd *acc)
+{
+    cd a[2 * PB + 1];
+    a[PB] = acc[0];
+#pragma unroll
+    for (int m = 1; m <= PB; ++m) {
+        cd E = acc[2 * m - 1], F = acc[2 * m];
+        cd lo = mk(E.x + F.y, E.y - F.x);              // E - i F
+        a[PB + m] = mk(E.x - F.y, E.y + F.x);
+        a[PB - m] = (m & 1) ? neg(lo) : lo;
+    }
+#pragma unroll
+    for (int e = 0; e < 2 * PB + 1; ++e) acc[e] = a[e];
 }
 
 __device__ __forceinline__ double shfl_xor_d(double v, int m)
@@ -1300,6 +1322,7 @@ __device__ __forceinline__ void p2qbxl_body(const DevGeom &g, int nd, const int 
                         p2qbxl_pair<PB>(g.omega, iomega, cx, cy, SX[f], SY[f], NX[f], NY[f], QS[f], QD[f], acc);
                 }
             }
+            p2qbxl_alpha<PB>(acc);
             // sum the parts of each centre in part order
 #pragma unroll
             for (int e0 = 0; e0 < NE; e0 += P2Q_RED) {
@@ -1365,6 +1388,7 @@ __device__ __forceinline__ void p2qbxl_direct_body(const DevGeom &g, int nd, int
             for (int j = part; j < g.ns; j += parts)
                 p2qbxl_pair<PB>(g.omega, iomega, cx, cy, g.sx[j], g.sy[j], g.snx[j], g.sny[j],
                                 qs[(long long)d * g.ns + j], qd[(long long)d * g.ns + j], acc);
+        p2qbxl_alpha<PB>(acc);
         p2qbxl_finish<PB>(acc, G, p, active && part == 0,
                           coef + (long long)d * ncoef * g.nc + (active ? i : 0), g.nc, false);
     }

@@ -73,3 +73,26 @@ def test_hankel_forms_meet(ctx, which):
     err = np.abs(u - ref) / np.abs(ref)
     print(f"{which}: {err.max():.2e} at x = {x[err.argmax()]:g}", flush=True)
     assert err.max() <= 4e-15
+
+
+# The coefficient sums at the smallest and largest order of each kernel
+# variant, S and D together, direct and FMM, one and three densities.  The
+# bounds are those of the direct and FMM comparisons elsewhere: rounding grows
+# with the order (1e-11 up to 40), the FMM adds its eps.
+@pytest.mark.parametrize("p", [0, 1, 8, 9, 12, 13, 14, 15, 16, 17, 25, 33, 40])
+def test_coefficient_sums_at_variant_edges(ctx, p):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(24, 16, lobes=3, amp=0.3)
+    omega = 9.0
+    ss, sd = _densities(g, 3, 41)
+    tc = np.arange(g.n, dtype=np.int32)
+    ref = oracle.direct_qbx(omega, p, g, g.sx, g.sy, ss, sd, tgt_ctr=tc)
+    for direct, tol in ((True, 1e-11), (False, 1e-9)):
+        geo = qbx.Geometry(ctx, g, omega, 1e-9, g.sx, g.sy, tc,
+                           qbx.options(p=p, direct=direct, p_add=-1 if p < 20 else 3 * p))
+        u = geo.eval(_dev(ss), _dev(sd)).cpu().numpy()
+        err = np.linalg.norm(u - ref) / np.linalg.norm(ref)
+        print(f"p {p} direct {direct}: {err:.2e}", flush=True)
+        assert err <= tol
+        one = geo.eval(_dev(ss[1:2]), _dev(sd[1:2])).cpu().numpy()
+        assert np.array_equal(one[0], u[1])
