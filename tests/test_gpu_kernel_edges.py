@@ -96,3 +96,32 @@ def test_coefficient_sums_at_variant_edges(ctx, p):
         assert err <= tol
         one = geo.eval(_dev(ss[1:2]), _dev(sd[1:2])).cpu().numpy()
         assert np.array_equal(one[0], u[1])
+
+
+# Gram-Schmidt products with vector counts around the rows of a block and the
+# rows of the final sums' blocks, lengths around a chunk and past 64 chunks;
+# panel interpolation with panel counts around a block's, and panels too long
+# for LDS.  The rounding of sums of n products of unit-variance entries is
+# below 1e-12 sqrt(n) at these lengths.
+@pytest.mark.parametrize("n,k", [(1, 1), (1023, 3), (1024, 8), (1025, 9), (70001, 5)])
+def test_gram_schmidt_edges(ctx, n, k):
+    r = np.random.default_rng(n + k)
+    V, w = inputs.complex_gaussian(r, (k, n)), inputs.complex_gaussian(r, (n,))
+    dV, dw, h = _dev(V), _dev(w), _dev(np.zeros(k, dtype=np.complex128))
+    ctx.krylov_dot(dV, k, dw, h)
+    ref = V.conj() @ w
+    assert np.abs(h.cpu().numpy() - ref).max() <= 1e-13 * max(1.0, np.sqrt(n)) * 10
+    ctx.krylov_update(dV, k, h, dw)
+    out = w - ref @ V
+    assert np.abs(dw.cpu().numpy() - out).max() <= 1e-12 * max(1.0, np.abs(out).max())
+
+
+@pytest.mark.parametrize("panels,q,qs", [(1, 1, 1), (7, 16, 64), (8, 8, 40), (9, 16, 32), (3, 90, 90)])
+def test_upsample_edges(ctx, panels, q, qs):
+    r = np.random.default_rng(panels)
+    L, x = r.standard_normal((qs, q)), inputs.complex_gaussian(r, (panels * q,))
+    ys, yd = _dev(np.zeros(panels * qs, dtype=np.complex128)), _dev(np.zeros(panels * qs, dtype=np.complex128))
+    ctx.upsample(_dev(L), q, qs, _dev(x), 2.0 - 1.0j, ys=ys, yd=yd)
+    ref = (x.reshape(panels, q) @ L.T).ravel()
+    assert np.abs(yd.cpu().numpy() - ref).max() <= 1e-12
+    assert np.abs(ys.cpu().numpy() - (2.0 - 1.0j) * ref).max() <= 1e-11
