@@ -59,6 +59,8 @@ struct QbxLane {
     hipEvent_t ev_fork = nullptr, ev_x = nullptr, ev_q = nullptr, ev_m = nullptr;
 };
 
+constexpr size_t kTmpKeep = 2, kTmpKeepBytes = size_t(16) << 20;
+
 struct qbx_ctx_s {
     // the caller's handle and every geometry made on the context hold a
     // reference; the context is torn down when the last one goes, so a
@@ -86,6 +88,10 @@ struct qbx_ctx_s {
     // workspace of qbx_krylov_dot (partial sums), grown on demand
     cd *kw = nullptr;
     size_t kw_cap = 0;
+    // idle device blocks of the area-query calls (DevTmp), at most kTmpKeep of
+    // at most kTmpKeepBytes; freed with the context
+    std::mutex tmp_mu;
+    std::vector<std::pair<void *, size_t>> tmp_free;
     // the thread inside a call on this context (nested calls of that thread
     // count in depth), and the message of the last failed call
     std::atomic<std::thread::id> owner{};
@@ -1652,6 +1658,7 @@ void ctx_release(qbx_ctx_s *ctx)
     if (ctx->ev_in) (void)hipEventDestroy(ctx->ev_in);
     if (ctx->ev_out) (void)hipEventDestroy(ctx->ev_out);
     if (ctx->kw) (void)hipFree(ctx->kw);
+    for (auto &b : ctx->tmp_free) (void)hipFree(b.first);
     delete ctx;
 }
 
@@ -2361,22 +2368,55 @@ qbx_status qbx_geom_graph(qbx_geom G, int32_t enable)
 // ---- area queries and association on the device ---------------------------
 namespace {
 
-// Temporary device buffers of one call, freed when it returns.
+// Temporary device buffers of one call.  A call that has waited for its
+// stream leaves them to the next call on the context, within bounds (each
+// allocation and release costs more than the small kernels between).
 struct DevTmp {
-    std::vector<void *> ptrs;
+    qbx_ctx_s *c;
+    std::vector<std::pair<void *, size_t>> blocks;
     hipError_t err = hipSuccess;
-    template <class T> T *alloc(size_t n)
+    bool idle = false;                  // the stream that used the blocks has been waited for
+    explicit DevTmp(qbx_ctx_s *ctx) : c(ctx) {}
+    unsigned char *block(size_t n)
     {
+        n = std::max<size_t>(n, 256);
+        {
+            std::lock_guard<std::mutex> lk(c->tmp_mu);
+            for (size_t i = 0; i < c->tmp_free.size(); ++i)
+                if (c->tmp_free[i].second >= n) {
+                    blocks.push_back(c->tmp_free[i]);
+                    c->tmp_free.erase(c->tmp_free.begin() + (long)i);
+                    return static_cast<unsigned char *>(blocks.back().first);
+                }
+        }
         void *q = nullptr;
-        if (err == hipSuccess) err = hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(T));
+        if (err == hipSuccess) err = hipMalloc(&q, n);
         if (err != hipSuccess) return nullptr;
-        ptrs.push_back(q);
-        return static_cast<T *>(q);
+        blocks.push_back({q, n});
+        return static_cast<unsigned char *>(q);
     }
     ~DevTmp()
     {
-        for (void *q : ptrs) (void)hipFree(q);
+        for (auto &b : blocks) {
+            {
+                std::lock_guard<std::mutex> lk(c->tmp_mu);
+                if (idle && b.second <= kTmpKeepBytes && c->tmp_free.size() < kTmpKeep) {
+                    c->tmp_free.push_back(b);
+                    continue;
+                }
+            }
+            (void)hipFree(b.first);
+        }
     }
+    DevTmp(const DevTmp &) = delete;
+    DevTmp &operator=(const DevTmp &) = delete;
+};
+
+// What a call's kernels report, copied to the host at its waits.
+struct AqCtrl {
+    int64_t total[2];
+    unsigned long long nfail;
+    int err, pad;
 };
 
 AQTree aq_tree(const qbx_geom_s *G)
@@ -2391,28 +2431,13 @@ AQTree aq_tree(const qbx_geom_s *G)
     return t;
 }
 
-// Exclusive scan of n device counts into start[0..n] (device), on the host.
-hipError_t scan_counts(const int32_t *cnt, int64_t n, int64_t *start, int64_t *total, hipStream_t s)
+// Waits for the stream and takes the call's report.
+qbx_status aq_check(hipError_t e, const AqCtrl *d_ctrl, AqCtrl &h, hipStream_t s, const char *what)
 {
-    std::vector<int32_t> h((size_t)n);
-    std::vector<int64_t> st((size_t)n + 1, 0);
-    hipError_t e = n ? hipMemcpyAsync(h.data(), cnt, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s) : hipSuccess;
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return e;
-    for (int64_t i = 0; i < n; ++i) st[i + 1] = st[i] + h[i];
-    *total = st[n];
-    e = hipMemcpyAsync(start, st.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    return e;
-}
-
-qbx_status aq_check(hipError_t e, const int *d_err, hipStream_t s, const char *what)
-{
-    int herr = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&herr, d_err, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&h, d_ctrl, sizeof(AqCtrl), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(QBX_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
-    if (herr) return fail(QBX_E_DEVICE, std::string(what) + ": traversal stack exceeded");
+    if (h.err) return fail(QBX_E_DEVICE, std::string(what) + ": traversal stack exceeded");
     return QBX_OK;
 }
 
@@ -2429,21 +2454,21 @@ qbx_status qbx_geom_area_query(qbx_geom G, int64_t n, const double *qx, const do
     if (e != hipSuccess) return fail(QBX_E_DEVICE, std::string("hipSetDevice: ") + hipGetErrorString(e));
     hipStream_t s = G->ctx->stream;
     AQTree t = aq_tree(G);
-    DevTmp tmp;
-    int32_t *cnt = tmp.alloc<int32_t>((size_t)n);
-    int *err = tmp.alloc<int>(1);
+    DevTmp tmp(G->ctx);
+    const size_t a_cnt = DeviceArena::aligned(sizeof(int32_t) * (size_t)n), a_ctrl = DeviceArena::aligned(sizeof(AqCtrl));
+    unsigned char *blk = tmp.block(a_ctrl + a_cnt + scan_scratch(n));
     if (tmp.err != hipSuccess) return fail(QBX_E_NOMEM, "area query buffers");
-    e = hipMemsetAsync(err, 0, sizeof(int), s);
-    if (e == hipSuccess) e = launch_area_query(t, n, qx, qy, qr, cnt, nullptr, nullptr, err, s);
-    qbx_status st = aq_check(e, err, s, "area query (count)");
+    AqCtrl *ctrl = reinterpret_cast<AqCtrl *>(blk), h{};
+    int32_t *cnt = reinterpret_cast<int32_t *>(blk + a_ctrl);
+    e = hipMemsetAsync(ctrl, 0, sizeof(AqCtrl), s);
+    if (e == hipSuccess) e = launch_area_query(t, n, qx, qy, qr, cnt, nullptr, nullptr, &ctrl->err, s);
+    if (e == hipSuccess) e = launch_scan(n, cnt, start, &ctrl->total[0], blk + a_ctrl + a_cnt, s);
+    if (e == hipSuccess && leaves) e = launch_area_query(t, n, qx, qy, qr, nullptr, start, leaves, &ctrl->err, s);
+    qbx_status st = aq_check(e, ctrl, h, s, "area query");
     if (st != QBX_OK) return st;
-    int64_t total = 0;
-    e = scan_counts(cnt, n, start, &total, s);
-    if (e != hipSuccess) return fail(QBX_E_DEVICE, std::string("area query (scan): ") + hipGetErrorString(e));
-    if (total_out) *total_out = total;
-    if (!leaves) return QBX_OK;
-    e = launch_area_query(t, n, qx, qy, qr, nullptr, start, leaves, err, s);
-    return aq_check(e, err, s, "area query (fill)");
+    tmp.idle = true;
+    if (total_out) *total_out = h.total[0];
+    return QBX_OK;
 }
 
 qbx_status qbx_geom_points_near(qbx_geom G, int32_t which, int64_t n, const double *qx, const double *qy,
@@ -2455,15 +2480,17 @@ qbx_status qbx_geom_points_near(qbx_geom G, int32_t which, int64_t n, const doub
     hipError_t e = hipSetDevice(G->ctx->device);
     if (e != hipSuccess) return fail(QBX_E_DEVICE, std::string("hipSetDevice: ") + hipGetErrorString(e));
     hipStream_t s = G->ctx->stream;
-    DevTmp tmp;
-    int *err = tmp.alloc<int>(1);
+    DevTmp tmp(G->ctx);
+    AqCtrl *ctrl = reinterpret_cast<AqCtrl *>(tmp.block(sizeof(AqCtrl))), h{};
     if (tmp.err != hipSuccess) return fail(QBX_E_NOMEM, "points_near buffers");
     const DevGeom &g = G->g;
-    e = hipMemsetAsync(err, 0, sizeof(int), s);
+    e = hipMemsetAsync(ctrl, 0, sizeof(AqCtrl), s);
     if (e == hipSuccess)
-        e = which == 0 ? launch_points_near(aq_tree(G), n, qx, qy, qr, g.src_begin, g.src_end, g.sx, g.sy, hit_out, err, s)
-                       : launch_points_near(aq_tree(G), n, qx, qy, qr, g.ctr_begin, g.ctr_end, g.cx, g.cy, hit_out, err, s);
-    return aq_check(e, err, s, "points_near");
+        e = which == 0 ? launch_points_near(aq_tree(G), n, qx, qy, qr, g.src_begin, g.src_end, g.sx, g.sy, hit_out, &ctrl->err, s)
+                       : launch_points_near(aq_tree(G), n, qx, qy, qr, g.ctr_begin, g.ctr_end, g.cx, g.cy, hit_out, &ctrl->err, s);
+    qbx_status st = aq_check(e, ctrl, h, s, "points_near");
+    tmp.idle = st == QBX_OK;
+    return st;
 }
 
 qbx_status qbx_geom_associate(qbx_geom G, int64_t n_tgt, const double *tx, const double *ty,
@@ -2477,23 +2504,25 @@ qbx_status qbx_geom_associate(qbx_geom G, int64_t n_tgt, const double *tx, const
     const Plan &pl = G->pl;
     AQTree t = aq_tree(G);
     int64_t nkey = (int64_t)kAqKeysPerBox * pl.n_boxes();
-    // radii in tree order
-    std::vector<double> hcr((size_t)pl.nc), hsh((size_t)pl.ns);
-    for (int64_t k = 0; k < pl.nc; ++k) hcr[k] = pl.cr[pl.ctr_order[k]];
-    for (int64_t k = 0; k < pl.ns; ++k) hsh[k] = pl.sh[pl.src_order[k]];
-    DevTmp tmp;
-    double *dcr = tmp.alloc<double>(hcr.size()), *dsh = tmp.alloc<double>(hsh.size());
-    int32_t *ccnt = tmp.alloc<int32_t>(nkey), *scnt = tmp.alloc<int32_t>(nkey);
-    int64_t *cstart = tmp.alloc<int64_t>(nkey + 1), *sstart = tmp.alloc<int64_t>(nkey + 1);
-    int *err = tmp.alloc<int>(1);
-    unsigned long long *nfail = tmp.alloc<unsigned long long>(1);
+    // radii in tree order, centres then sources
+    std::vector<double> hr((size_t)(pl.nc + pl.ns));
+    for (int64_t k = 0; k < pl.nc; ++k) hr[k] = pl.cr[pl.ctr_order[k]];
+    for (int64_t k = 0; k < pl.ns; ++k) hr[pl.nc + k] = pl.sh[pl.src_order[k]];
+    DevTmp tmp(G->ctx);
+    // one block: report, counts (centres then sources), offsets, scan scratch, radii
+    const size_t a_ctrl = DeviceArena::aligned(sizeof(AqCtrl)), a_cnt = DeviceArena::aligned(sizeof(int32_t) * 2 * (size_t)nkey),
+                 a_start = DeviceArena::aligned(sizeof(int64_t) * (size_t)(nkey + 1)), a_scan = DeviceArena::aligned(scan_scratch(nkey));
+    unsigned char *blk = tmp.block(a_ctrl + a_cnt + 2 * a_start + a_scan + sizeof(double) * hr.size());
     if (tmp.err != hipSuccess) return fail(QBX_E_NOMEM, "associate buffers");
-    e = hipMemcpyAsync(dcr, hcr.data(), sizeof(double) * hcr.size(), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(dsh, hsh.data(), sizeof(double) * hsh.size(), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(ccnt, 0, sizeof(int32_t) * nkey, s);
-    if (e == hipSuccess) e = hipMemsetAsync(scnt, 0, sizeof(int32_t) * nkey, s);
-    if (e == hipSuccess) e = hipMemsetAsync(err, 0, sizeof(int), s);
-    if (e == hipSuccess) e = hipMemsetAsync(nfail, 0, sizeof(unsigned long long), s);
+    AqCtrl *ctrl = reinterpret_cast<AqCtrl *>(blk), h{};
+    int32_t *ccnt = reinterpret_cast<int32_t *>(blk + a_ctrl), *scnt = ccnt + nkey;
+    int64_t *cstart = reinterpret_cast<int64_t *>(blk + a_ctrl + a_cnt);
+    int64_t *sstart = reinterpret_cast<int64_t *>(blk + a_ctrl + a_cnt + a_start);
+    void *scan = blk + a_ctrl + a_cnt + 2 * a_start;
+    double *dcr = reinterpret_cast<double *>(blk + a_ctrl + a_cnt + 2 * a_start + a_scan), *dsh = dcr + pl.nc;
+    int *err = &ctrl->err;
+    e = hipMemcpyAsync(dcr, hr.data(), sizeof(double) * hr.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemsetAsync(blk, 0, a_ctrl + a_cnt, s);
     // every centre enters the regions its eligibility square meets, every
     // source those its sh/4 square meets (squares a relative 1e-12 wider:
     // the final tests are exact)
@@ -2504,17 +2533,15 @@ qbx_status qbx_geom_associate(qbx_geom G, int64_t n_tgt, const double *tx, const
     if (e == hipSuccess)
         e = launch_region_lists(t, pl.ns, G->g.sx, G->g.sy, dsh, 0.25 * widen, scnt, nullptr, nullptr, nullptr,
                                 err, s);
-    qbx_status st = aq_check(e, err, s, "associate (count)");
+    if (e == hipSuccess) e = launch_scan(nkey, ccnt, cstart, &ctrl->total[0], scan, s);
+    if (e == hipSuccess) e = launch_scan(nkey, scnt, sstart, &ctrl->total[1], scan, s);
+    qbx_status st = aq_check(e, ctrl, h, s, "associate (count)");
     if (st != QBX_OK) return st;
-    int64_t ctot = 0, stot = 0;
-    e = scan_counts(ccnt, nkey, cstart, &ctot, s);
-    if (e == hipSuccess) e = scan_counts(scnt, nkey, sstart, &stot, s);
-    if (e != hipSuccess) return fail(QBX_E_DEVICE, std::string("associate (scan): ") + hipGetErrorString(e));
-    int32_t *clist = tmp.alloc<int32_t>((size_t)ctot), *slist = tmp.alloc<int32_t>((size_t)stot);
+    int32_t *clist = reinterpret_cast<int32_t *>(tmp.block(sizeof(int32_t) * (size_t)(h.total[0] + h.total[1])));
     if (tmp.err != hipSuccess) return fail(QBX_E_NOMEM, "associate lists");
+    int32_t *slist = clist + h.total[0];
     // the count arrays serve again as fill cursors
-    e = hipMemsetAsync(ccnt, 0, sizeof(int32_t) * nkey, s);
-    if (e == hipSuccess) e = hipMemsetAsync(scnt, 0, sizeof(int32_t) * nkey, s);
+    e = hipMemsetAsync(ccnt, 0, a_cnt, s);
     if (e == hipSuccess)
         e = launch_region_lists(t, pl.nc, G->g.cx, G->g.cy, dcr, (1.0 + ea) * widen, nullptr, cstart, ccnt,
                                 clist, err, s);
@@ -2526,14 +2553,11 @@ qbx_status qbx_geom_associate(qbx_geom G, int64_t n_tgt, const double *tx, const
     a.sx = G->g.sx; a.sy = G->g.sy; a.sh = dsh;
     a.cstart = cstart; a.sstart = sstart; a.clist = clist; a.slist = slist;
     a.ea = ea;
-    if (e == hipSuccess) e = launch_associate(t, a, n_tgt, tx, ty, tgt_ctr_out, nfail, s);
-    st = aq_check(e, err, s, "associate");
+    if (e == hipSuccess) e = launch_associate(t, a, n_tgt, tx, ty, tgt_ctr_out, &ctrl->nfail, s);
+    st = aq_check(e, ctrl, h, s, "associate");
     if (st != QBX_OK) return st;
-    unsigned long long hf = 0;
-    e = hipMemcpyAsync(&hf, nfail, sizeof(hf), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail(QBX_E_DEVICE, std::string("associate: ") + hipGetErrorString(e));
-    if (n_fail_out) *n_fail_out = (int64_t)hf;
+    tmp.idle = true;
+    if (n_fail_out) *n_fail_out = (int64_t)h.nfail;
     return QBX_OK;
 }
 

@@ -23,6 +23,11 @@ struct AQTree {
 // without points, so such a quadrant belongs to no leaf).
 constexpr int kAqKeysPerBox = 5;
 
+// Exclusive scan of n device counts into start[0..n]; *total (device) = their
+// sum.  scratch: scan_scratch(n) bytes of device memory.
+size_t scan_scratch(int64_t n);
+hipError_t launch_scan(int64_t n, const int32_t *cnt, int64_t *start, int64_t *total, void *scratch, hipStream_t s);
+
 // Area queries for n squares C_r(c), c = (qx[i], qy[i]), r = qr[i].
 // count pass (list == nullptr): cnt[i] = number of leaves met;
 // fill pass: the leaves of query i go to list[start[i] ..], in the order the

@@ -125,3 +125,26 @@ def test_upsample_edges(ctx, panels, q, qs):
     ref = (x.reshape(panels, q) @ L.T).ravel()
     assert np.abs(yd.cpu().numpy() - ref).max() <= 1e-12
     assert np.abs(ys.cpu().numpy() - (2.0 - 1.0j) * ref).max() <= 1e-11
+
+
+# Offsets of area queries around the sizes of the scan's blocks (2048 counts)
+# and past one round of its block sums (256 blocks): one call over n squares
+# against calls over parts of them, leaf by leaf.
+@pytest.mark.parametrize("n", [0, 1, 2047, 2048, 2049, 530001])
+def test_area_query_offsets(ctx, n):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(40, 16, lobes=5, amp=0.3)
+    geo = qbx.Geometry(ctx, g, 5.0, 1e-8, g.sx, g.sy, np.arange(g.n, dtype=np.int32), qbx.options(p=8))
+    r = np.random.default_rng(n)
+    x, y = _dev(r.uniform(-1.4, 1.4, n)), _dev(r.uniform(-1.4, 1.4, n))
+    rad = _dev(r.uniform(-0.02, 0.06, n))                   # a quarter of them empty
+    start, leaves = geo.area_query(x, y, rad)
+    starts, parts, base = [], [], 0
+    for i in range(0, n, 1000):
+        s, l = geo.area_query(x[i:i + 1000].contiguous(), y[i:i + 1000].contiguous(), rad[i:i + 1000].contiguous())
+        starts.append(s[:-1] + base)
+        parts.append(l)
+        base += int(s[-1])
+    assert int(start[-1]) == base and leaves.numel() == base
+    if n:
+        assert torch.equal(start[:-1], torch.cat(starts)) and torch.equal(leaves, torch.cat(parts))
