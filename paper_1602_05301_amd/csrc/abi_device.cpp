@@ -326,9 +326,9 @@ struct qbx_geom_s {
     // per-eval scratch, sized for kDensChunk densities
     DeviceArena scratch;
     cd *qs = nullptr, *qd = nullptr, *mp = nullptr, *loc = nullptr, *coef = nullptr;
-    // radial sequences: J_n per P2M source and per L2QBXL centre (n-major)
+    // radial sequences: J_n per P2M source and per L2QBXL centre
     // geometry-only sequences, resident: the P2M and X-list P2L bases (in
-    // the view g) and J_n(omega |m_b - c|) per L2QBXL centre (n-major),
+    // the view g) and J_n(omega |m_b - c|) per L2QBXL centre (a row each),
     // built on the first evaluation
     int srad_rows = 0, crad_rows = 0;
     int l2q_cap = 1;              // centres per L2QBXL item (at most)
@@ -626,10 +626,14 @@ qbx_status upload(qbx_geom_s *G)
         }
     }
     if (!table_ok) return fail(QBX_E_NOMEM, "translation tables too large");
-    g.m2m_mf = ar.upload(m2m); g.l2l_mf = ar.upload(l2l); g.m2l_mf = ar.upload(m2l);
+    g.m2m_mf = ar.upload(m2m);
     g.far32 = pl.opt.far_fp32 ? 1 : 0;
+    g.l2l_mf = g.m2l_mf = nullptr;
     g.m2l_mf32 = g.l2l_mf32 = nullptr;
-    if (g.far32) {
+    if (!g.far32) {
+        g.l2l_mf = ar.upload(l2l);
+        g.m2l_mf = ar.upload(m2l);
+    } else {
         // the scaled entries are bounded by one, so complex float holds them
         auto to32 = [](const std::vector<cd> &v) {
             std::vector<cf> o(v.size());
@@ -754,8 +758,30 @@ qbx_status upload(qbx_geom_s *G)
         std::stable_sort(leaves.begin(), leaves.end(), [&](int a, int c) {
             return pl.ctr_end[a] - pl.ctr_begin[a] > pl.ctr_end[c] - pl.ctr_begin[c];
         });
+        {
+            int nblk = (2 * pl.p + 1 + QBLK - 1) / QBLK;
+            std::vector<int2> rng((size_t)std::max(pl.nlev, 1) * nblk, make_int2(0, 0));
+            std::vector<char> has(std::max(pl.nlev, 1), 0);
+            for (int b : leaves) has[pl.lev[b]] = 1;
+            for (int l = 0; l < pl.nlev && !pl.opt.direct; ++l) {
+                if (!has[l]) continue;
+                KeptRows kr = l2qbxl_kept(pl, l);
+                for (int i = 0; i < nblk; ++i) {
+                    int l0 = -pl.p + QBLK * i, lo = 2 * pl.P[l], hi = 0;
+                    for (int e = 0; e < QBLK && l0 + e <= pl.p; ++e) {
+                        lo = std::min(lo, kr.lo[l0 + e + pl.p]);
+                        hi = std::max(hi, kr.hi[l0 + e + pl.p]);
+                    }
+                    rng[(size_t)l * nblk + i] = make_int2(l0 - (hi - pl.P[l]), l0 + QBLK - 1 - (lo - pl.P[l]));
+                }
+            }
+            g.l2q_rng = ar.upload(rng);
+        }
         int cap = l2qbxl_item_cap(G->l2q.Pmax, G->l2q.Pmax + pl.p + 8);
         std::vector<std::pair<int, int>> runs;
+        std::vector<int> leaf_of(std::max<int64_t>(pl.nc, 1), 0);
+        for (int b : leaves)
+            for (int c = pl.ctr_begin[b]; c < pl.ctr_end[b]; ++c) leaf_of[c] = b;
         for (int b : leaves)
             for (int c = pl.ctr_begin[b]; c < pl.ctr_end[b]; c += cap)
                 runs.push_back({c, std::min(c + cap, (int)pl.ctr_end[b])});
@@ -773,12 +799,15 @@ qbx_status upload(qbx_geom_s *G)
                 }
             if (pick < 0) {
                 pick = (int)used.size();
-                items.insert(items.end(), 2 * L2Q_SEGS, 0);
+                items.insert(items.end(), L2Q_ITEM, 0);
                 used.push_back(0);
                 nrun.push_back(0);
             }
-            items[(size_t)pick * 2 * L2Q_SEGS + 2 * nrun[pick]] = r.first;
-            items[(size_t)pick * 2 * L2Q_SEGS + 2 * nrun[pick] + 1] = r.second;
+            int *it = items.data() + (size_t)pick * L2Q_ITEM + 4 * nrun[pick];
+            it[0] = r.first;
+            it[1] = r.second;
+            it[2] = leaf_of[r.first];
+            it[3] = pl.lev[it[2]];
             ++nrun[pick];
             used[pick] += sz;
             if (used[pick] < cap && nrun[pick] < L2Q_SEGS) open[cap - used[pick]].push_back(pick);

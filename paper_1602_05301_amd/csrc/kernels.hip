@@ -56,13 +56,12 @@ __global__ void k_charges(DevGeom g, int nd, const cd *sig_s, const cd *sig_d, c
     charges_body(g, nd, sig_s, sig_d, qs, qd, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
-constexpr int QBLK = 8;       // l values per lane; the planner keeps P_l >= p + QBLK
-
 // ---------------------------------------------------------------------------
 // Radial sequences, one lane per source / centre (so every lane does a
-// whole recurrence), written n-major: element n of item i at rad[n * count + i].
+// whole recurrence).
 //   (k_src_bas, P2M's basis, is built the same way, below)
-//   k_ctr_rad: J_n(omega |m_b - c|), n = 0..P_b+p+7, c in such a leaf
+//   k_ctr_rad: J_n(omega |m_b - c|), n = 0..P_b+p+7, c in such a leaf, at
+//   rad[c * rows + n], zero above
 // Miller's recurrence rewrites earlier values when it rescales and
 // normalises at the end, so it runs in LDS ([rows][lanes]) and each lane
 // then copies its own column out.
@@ -103,19 +102,22 @@ __global__ void k_src_bas(DevGeom g, cd *bas)
 __device__ __forceinline__ void ctr_rad_body(const DevGeom &g, int rows, double *rad, BlockId bid)
 {
     extern __shared__ double lds_raw[];
-    int lanes = blockDim.x;
-    int c = bid.x * lanes + threadIdx.x;
+    int lanes = blockDim.x, ls = lanes + 1;             // padded rows: the copy below reads columns
+    int c0 = bid.x * lanes, c = c0 + threadIdx.x;
     int N = -1;
     if (c < g.nc) {
         int b = g.ctr_box[c];
         if (b >= 0) {
             N = g.Plev[g.blev[b]] + g.p + QBLK - 1;
             double dx = g.bcx[b] - g.cx[c], dy = g.bcy[b] - g.cy[c];
-            besselj_seq(g.omega * sqrt(dx * dx + dy * dy), N, lds_raw + threadIdx.x, lanes);
+            besselj_seq(g.omega * sqrt(dx * dx + dy * dy), N, lds_raw + threadIdx.x, ls);
         }
     }
-    (void)rows;
-    for (int n = 0; n <= N; ++n) rad[(long long)n * g.nc + c] = lds_raw[n * lanes + threadIdx.x];
+    for (int n = N + 1; n < rows; ++n) lds_raw[n * ls + threadIdx.x] = 0.0;
+    __syncthreads();
+    int cnt = min(lanes, g.nc - c0) * rows;
+    for (int i = threadIdx.x; i < cnt; i += lanes)
+        rad[(long long)c0 * rows + i] = lds_raw[i % rows * ls + i / rows];
 }
 
 __global__ void k_ctr_rad(DevGeom g, int rows, double *rad)
@@ -123,11 +125,13 @@ __global__ void k_ctr_rad(DevGeom g, int rows, double *rad)
     ctr_rad_body(g, rows, rad, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
-// lanes per block of a Miller kernel: [rows][lanes] doubles within 64 KiB
+// lanes per block of a Miller kernel: [rows][lanes + 1] doubles within 64 KiB
+static size_t rad_lds(int rows, int lanes) { return (size_t)rows * (lanes + 1) * sizeof(double); }
+
 static int rad_lanes(int rows)
 {
     int lanes = 64;
-    while (lanes > 1 && (size_t)rows * lanes * sizeof(double) > 64 * 1024) lanes >>= 1;
+    while (lanes > 1 && rad_lds(rows, lanes) > 64 * 1024) lanes >>= 1;
     return lanes;
 }
 
@@ -1673,13 +1677,23 @@ __global__ void k_wsum(DevGeom g, int nd, const int *leaf_list, const int *leaf_
 // fit).  A leaf's centres alone would leave a third of the lanes idle on a
 // typical curve (about 11 centres per leaf against 16 slots).  Each centre's
 // arithmetic is the same whichever item it lands in.
+//
+// The n range of a block is the one whose terms count (l2q_rng): in a box
+// small against the wavelength an order l > 0 takes the locals of k from about
+// l on, l < 0 those up to about l, and only the block about l = 0 both.
+// L2QBXL_FIGURES
 // ---------------------------------------------------------------------------
 constexpr int L2Q_THREADS = 256;   // lanes per item: 16 slots x 4 l-blocks x 4 quarters
+constexpr int L2Q_PAD = 16;        // zeros around a run's locals and a centre's J_n
+
+// Entries of a centre's J_n row in LDS (n = -N..N and zeros around, N = rows - 1).
+__host__ __device__ constexpr int l2q_jrow(int rows) { return 2 * (rows - 1) + 1 + 2 * L2Q_PAD; }
 
 size_t l2qbxl_lds_bytes(int P, int cap, int rows)
 {
     // one density's locals of every run, the centres' directions, their J_n rows
-    return sizeof(cd) * ((size_t)L2Q_SEGS * (2 * P + 1) + (size_t)cap) + sizeof(double) * (size_t)cap * rows;
+    return sizeof(cd) * ((size_t)L2Q_SEGS * (2 * P + 1 + 2 * L2Q_PAD) + (size_t)cap) +
+           sizeof(double) * (size_t)cap * l2q_jrow(rows);
 }
 
 int l2qbxl_item_cap(int Pmax, int rows)
@@ -1693,30 +1707,32 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
                                             const cd *loc, cd *coef, int cap, int rows, BlockId bid)
 {
     extern __shared__ double lds_raw[];
-    const int *it = items + 2 * L2Q_SEGS * bid.x;
+    const int *it = items + L2Q_ITEM * bid.x;
     // runs: centres [c0, c1) of leaf b, slots [so, so + c1 - c0), locals at Gb + go
-    int rc0[L2Q_SEGS], rb[L2Q_SEGS], rP[L2Q_SEGS], so[L2Q_SEGS + 1], go[L2Q_SEGS];
+    int rc0[L2Q_SEGS], rb[L2Q_SEGS], rl[L2Q_SEGS], rP[L2Q_SEGS], so[L2Q_SEGS + 1], go[L2Q_SEGS];
     int T = 0, gsum = 0;
 #pragma unroll
     for (int r = 0; r < L2Q_SEGS; ++r) {
-        int c0 = it[2 * r], c1 = it[2 * r + 1];
+        int c0 = it[4 * r], c1 = it[4 * r + 1];
         rc0[r] = c0;
+        rb[r] = it[4 * r + 2];
+        rl[r] = it[4 * r + 3];
         so[r] = T;
         go[r] = gsum;
-        rb[r] = c1 > c0 ? g.ctr_box[c0] : 0;
-        rP[r] = c1 > c0 ? g.Plev[g.blev[rb[r]]] : 0;
+        rP[r] = g.Plev[rl[r]];
         if (c1 > c0) {
             T += c1 - c0;
-            gsum += 2 * rP[r] + 1;
+            gsum += 2 * rP[r] + 1 + 2 * L2Q_PAD;
         }
     }
     so[L2Q_SEGS] = T;
     int p = g.p, nq = 2 * p + 1;
     int nblk = (nq + QBLK - 1) / QBLK;
     int tid = threadIdx.x;
+    const int JR = l2q_jrow(rows), J0 = rows - 1 + L2Q_PAD;   // row length, place of n = 0
     cd *Gb = reinterpret_cast<cd *>(lds_raw);          // [gsum]: run r's local at go[r]
     cd *U = Gb + gsum;                                 // [cap]
-    double *Jt = reinterpret_cast<double *>(U + cap);  // [cap][rows]
+    double *Jt = reinterpret_cast<double *>(U + cap);  // [cap][JR]
     auto run_of = [&](int t) {
         int r = 0;
 #pragma unroll
@@ -1729,11 +1745,18 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
         double rr = sqrt(dx * dx + dy * dy);
         U[t] = rr > 0.0 ? mk(dx / rr, dy / rr) : mk(1.0, 0.0);
     }
-    for (int i = tid; i < T * rows; i += blockDim.x) {
-        int n = i / T, t = i - n * T;
+    // J_n for both signs of n (J_{-n} = (-1)^n J_n), zero past the run's
+    // orders; 16 lanes read a centre's row
+    for (int t = tid >> 4; t < T; t += L2Q_THREADS / 16) {
         int r = run_of(t);
-        if (n <= rP[r] + p + QBLK - 1)
-            Jt[t * rows + n] = crad[(long long)n * g.nc + rc0[r] + t - so[r]];
+        const double *row = crad + (long long)(rc0[r] + t - so[r]) * rows;
+        double *J = Jt + t * JR + J0;
+#pragma unroll 4
+        for (int n = tid & 15; n < rows + L2Q_PAD; n += 16) {
+            double v = n < rows ? row[n] : 0.0;
+            J[n] = v;
+            J[-n] = (n & 1) ? -v : v;
+        }
     }
     for (int d = 0; d < nd; ++d) {
         if (d > 0) __syncthreads();                    // the previous density's readers are done
@@ -1741,9 +1764,10 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
             int r = 0;
 #pragma unroll
             for (int q = 1; q < L2Q_SEGS; ++q) r += i >= go[q] && so[q] < T;
-            int P = rP[r], np = 2 * P + 1, k = i - go[r] - P;
-            const double *iw = g.invW + g.Woff[g.blev[rb[r]]];
-            Gb[i] = iw[k < 0 ? -k : k] * loc[g.box_off[rb[r]] * nd + (long long)d * np + k + P];
+            int P = rP[r], np = 2 * P + 1, k = i - go[r] - L2Q_PAD - P;
+            const double *iw = g.invW + g.Woff[rl[r]];
+            Gb[i] = k >= -P && k <= P ? iw[k < 0 ? -k : k] * loc[g.box_off[rb[r]] * nd + (long long)d * np + k + P]
+                                      : mk(0.0, 0.0);
         }
         __syncthreads();
         int nitems = T * nblk;
@@ -1751,44 +1775,47 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
             int iq = it0 + tid / QSPLIT, sp = tid % QSPLIT;
             bool active = iq < nitems;
             int t = active ? iq % T : 0;
-            int l0 = -p + QBLK * (active ? iq / T : 0);
+            int blk = active ? iq / T : 0;
+            int l0 = -p + QBLK * blk;
             int r = run_of(t);
-            int P = rP[r];
             cd acc[QBLK], win[QBLK];
 #pragma unroll
-            for (int e = 0; e < QBLK; ++e) { acc[e] = mk(0.0, 0.0); win[e] = mk(0.0, 0.0); }
-            const double *jt = Jt + t * rows;
-            const cd *G = Gb + go[r] + P;
+            for (int e = 0; e < QBLK; ++e) acc[e] = mk(0.0, 0.0);
             cd u = U[t];
             int ci = rc0[r] + t - so[r];
             if (active) {
-                int na, nb;
-                chunk_of(l0 - P, l0 + QBLK - 1 + P, sp, &na, &nb);
-                if (na <= nb) {
-                    int k = l0 - (na - QBLK);                 // element of the first step
-                    cd ph = unit_ipow(conj(u), k);            // conj(u)^k
+                // this lane's quarter [na, nb) of the block's n range, in whole
+                // steps of QBLK: what a step adds past the range's end is
+                // zero (no such local, or no such J_n) or a term as good
+                const auto rng = g.l2q_rng + rl[r] * nblk + blk;
+                int n_lo = rng->x, n_end = rng->y + 1;
+                int cs = (n_end - n_lo + QSPLIT * QBLK - 1) / (QSPLIT * QBLK) * QBLK;
+                int na = n_lo + sp * cs, nb = min(na + cs, n_end);
+                const cd *G = Gb + go[r] + L2Q_PAD + rP[r] + l0 - na;    // G[-s]: local of order l0 - (na + s)
+                const double *J = Jt + t * JR + J0 + na;
+                if (na < nb) {
+                    cd ph = unit_ipow(conj(u), l0 - na + QBLK);          // conj(u)^k, k = l0 - n
+#pragma unroll
+                    for (int s = 0; s < QBLK; ++s) {
+                        win[s] = G[QBLK - s] * ph;
+                        ph = ph * u;
+                    }
 #pragma unroll 1
-                    for (int n0 = na - QBLK; n0 <= nb; n0 += QBLK) {
+                    for (int n0 = na; n0 < nb; n0 += QBLK) {
 #pragma unroll
                         for (int s = 0; s < QBLK; ++s) {
-                            int n = n0 + s;
-                            int kk = l0 - n;
-                            cd v = mk(0.0, 0.0);
-                            if (kk >= -P && kk <= P) v = G[kk] * ph;
+                            win[s] = G[-s] * ph;
                             ph = ph * u;
-                            win[s] = v;
-                            if (n >= na && n <= nb) {
-                                int an = n < 0 ? -n : n;
-                                double jn = jt[an];
-                                if (n < 0 && (an & 1)) jn = -jn;
+                            double jn = J[s];
 #pragma unroll
-                                for (int e = 0; e < QBLK; ++e) {
-                                    cd w = win[(s - e + QBLK) % QBLK];
-                                    acc[e].x = fma(w.x, jn, acc[e].x);
-                                    acc[e].y = fma(w.y, jn, acc[e].y);
-                                }
+                            for (int e = 0; e < QBLK; ++e) {
+                                cd w = win[(s - e + QBLK) % QBLK];
+                                acc[e].x = fma(w.x, jn, acc[e].x);
+                                acc[e].y = fma(w.y, jn, acc[e].y);
                             }
                         }
+                        G -= QBLK;
+                        J += QBLK;
                     }
                 }
             }
@@ -2166,7 +2193,7 @@ hipError_t launch_src_bas(const DevGeom &g, cd *sbas, hipStream_t s)
 {
     if (!g.ns) return hipSuccess;
     int lanes = rad_lanes(g.srow);
-    k_src_bas<<<(g.ns + lanes - 1) / lanes, lanes, (size_t)g.srow * lanes * sizeof(double), s>>>(g, sbas);
+    k_src_bas<<<(g.ns + lanes - 1) / lanes, lanes, rad_lds(g.srow, lanes), s>>>(g, sbas);
     QBX_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2437,7 +2464,7 @@ hipError_t launch_ctr_rad(const DevGeom &g, int nleaf, double *crad, int crad_ro
 {
     if (!nleaf || !g.nc) return hipSuccess;
     int lanes = rad_lanes(crad_rows);
-    k_ctr_rad<<<(g.nc + lanes - 1) / lanes, lanes, (size_t)crad_rows * lanes * sizeof(double), s>>>(
+    k_ctr_rad<<<(g.nc + lanes - 1) / lanes, lanes, rad_lds(crad_rows, lanes), s>>>(
         g, crad_rows, crad);
     QBX_LAUNCH_CHECK();
     return hipSuccess;
@@ -2576,7 +2603,7 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
         int rmax = 1;
         for (const auto &it : items) rmax = std::max(rmax, kind == FK_SRC_BAS ? it.h->srow : it.r.i0);
         int lanes = rad_lanes(rmax);
-        size_t lds = (size_t)rmax * lanes * sizeof(double);
+        size_t lds = rad_lds(rmax, lanes);
         for (const auto &it : items) {
             long long cnt = it.n > 0 ? (kind == FK_SRC_BAS ? it.h->ns : it.h->nc) : 0;
             long long b = (cnt + lanes - 1) / lanes;

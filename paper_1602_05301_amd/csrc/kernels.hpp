@@ -60,6 +60,9 @@ struct DevGeom {
     const QBX_G int *qsrc_idx;
     // X-list sources of the i-th box of the X-list P2L list: xsrc_idx[xsrc_start[i]..]
     const QBX_G int *xsrc_start, *xsrc_idx;
+    // L2QBXL: per level and block of QBLK orders l0.. (l0 = -p + QBLK i, at
+    // [level * blocks + i]) the range of n = l - k whose terms count
+    const QBX_G int2 *l2q_rng;
     const QBX_G int *src_box, *ctr_box;              // leaf (level >= 2) of each source / centre, or -1
     // Geometry-only bases, built on the first evaluation and kept: the P2M
     // row of every source in a leaf b of level >= 2, L_n(s - m_b) for
@@ -233,12 +236,14 @@ hipError_t launch_m2qbxl(const DevGeom &g, int nd, const int2 *pairs, const long
                          const int *leaf_pair_start, int nleaf, cd *coef, hipStream_t s);
 // J_n sequences of the L2QBXL centres (leaves of level >= 2), into crad
 hipError_t launch_ctr_rad(const DevGeom &g, int nleaf, double *crad, int crad_rows, hipStream_t s);
-// L2QBXL work items: L2Q_SEGS runs {c0, c1} of consecutive centres, each run
-// inside one leaf of level >= 2 (c0 == c1: unused), at most `cap` centres in
-// all.  l2qbxl_item_cap gives the largest cap (<= L2Q_CAP_MAX) whose staging
+// L2QBXL work items: L2Q_SEGS runs {c0, c1, b, level} of consecutive centres,
+// each run inside one leaf b of level >= 2 (c0 == c1: unused), at most `cap`
+// centres in all.  l2qbxl_item_cap gives the largest cap (<= L2Q_CAP_MAX) whose staging
 // fits the LDS budget for leaves of order up to Pmax and J_n rows of `rows`.
 constexpr int L2Q_SEGS = 4;
 constexpr int L2Q_CAP_MAX = 16;
+constexpr int L2Q_ITEM = 4 * L2Q_SEGS;   // ints per item
+constexpr int QBLK = 8;       // l values per lane; the planner keeps P_l >= p + QBLK
 int l2qbxl_item_cap(int Pmax, int rows);
 hipError_t launch_l2qbxl(const DevGeom &g, int nd, const int *items, int n, int Pmax, double *crad,
                          int crad_rows, int cap, const cd *loc, cd *coef, hipStream_t s);

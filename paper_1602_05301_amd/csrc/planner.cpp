@@ -247,12 +247,31 @@ namespace {
 
 constexpr double kLogZero = -1e30;
 
-double log_abs(long double v) { return v != 0.0L ? (double)std::log(std::fabs(v)) : kLogZero; }
-
+// log|J_n(x)|, n = 0..N, x > 0: the recurrence downward from far above both
+// N and x, normalised by J_0 + 2 (J_2 + J_4 + ...) = 1.  Good to a few digits,
+// which is all that a bound needs.
 std::vector<double> log_j(double x, int N)
 {
-    std::vector<double> out(N + 1);
-    for (int n = 0; n <= N; ++n) out[n] = log_abs(jnl(n, (long double)x));
+    std::vector<double> out(N + 1, kLogZero);
+    double top = std::max((double)N, x);
+    int M = (int)top + 20 + (int)(6.0 * std::cbrt(top + 1.0));
+    double f = 1.0, above = 0.0, shift = 0.0, sum = 0.0;    // f, sum in units of e^shift
+    for (int n = M; n >= 0; --n) {
+        if (n <= N && f != 0.0) out[n] = std::log(std::fabs(f)) + shift;
+        if (n % 2 == 0) sum += n ? 2.0 * f : f;
+        double below = (2.0 * n / x) * f - above;
+        above = f;
+        f = below;
+        if (std::fabs(f) > 1e200) {
+            f *= 1e-200;
+            above *= 1e-200;
+            sum *= 1e-200;
+            shift += 200.0 * std::log(10.0);
+        }
+    }
+    double norm = std::log(std::fabs(sum)) + shift;
+    for (double &v : out)
+        if (v > kLogZero) v -= norm;
     return out;
 }
 
@@ -372,6 +391,23 @@ KeptRows l2l_kept(const Plan &pl, int l)
     int Pp = pl.P[l], Pc = pl.P[l + 1];
     return kept_rows(Pc, Pp, false, log_j(pl.omega * pl.box_radius(l + 1) * std::sqrt(2.0), Pp + Pc),
                      local_profiles(pl.omega, pl.box_radius(l), Pp));
+}
+
+KeptRows l2qbxl_kept(const Plan &pl, int l)
+{
+    int P = pl.P[l];
+    double R = pl.box_radius(l);
+    Profiles pr = local_profiles(pl.omega, R, P);
+    KeptRows out;
+    for (double f : {1.0, 0.5, 0.1}) {          // distances of the centre, up to the box corner
+        KeptRows kr = kept_rows(pl.p, P, false, log_j(pl.omega * R * std::sqrt(2.0) * f, pl.p + P), pr);
+        if (out.lo.empty()) out = kr;
+        for (size_t i = 0; i < kr.lo.size(); ++i) {
+            out.lo[i] = std::min(out.lo[i], kr.lo[i]);
+            out.hi[i] = std::max(out.hi[i], kr.hi[i]);
+        }
+    }
+    return out;
 }
 
 std::vector<KeptRows> m2l_kept(const Plan &pl, int l, const std::vector<int> &dist2)

@@ -96,6 +96,10 @@ KeptRows m2m_kept(const Plan &pl, int l);                          // any child 
 KeptRows l2l_kept(const Plan &pl, int l);
 std::vector<KeptRows> m2l_kept(const Plan &pl, int l, const std::vector<int> &dist2);   // |offset|^2 in box sides
 
+// L2QBXL of a leaf at level l: rows -p..p, inputs the leaf's 2 P_l + 1 locals,
+// for a centre anywhere in the box.
+KeptRows l2qbxl_kept(const Plan &pl, int l);
+
 // Scaled translation matrices (row-major [out][in], complex<double>), zero
 // outside the kept entries.
 // M2M: child (level l+1, quadrant q) -> parent (level l).
