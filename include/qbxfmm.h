@@ -314,9 +314,8 @@ qbx_status qbx_eval_batch(qbx_ctx ctx, int32_t n_geom, const qbx_geom *geoms, co
  * each a sample of 4 whole evaluations with n_dens zero densities (HIP
  * events on the context's stream; the first pass warms up; temporary device
  * buffers; synchronises the stream), and each keeps its fastest sample.
- * Candidates: columns staged in LDS with w waves per tile, w the row-block
- * count of most V pairs (the default) or about half of it, and the
- * direct-load kernel; another candidate replaces the default only when at
+ * Candidates: columns staged in LDS with w waves per tile, w = 8 (4 for small
+ * orders; the default) or about half of it, and the direct-load kernel; another candidate replaces the default only when at
  * least 1% faster.  They compute the same sums in the same order, so results
  * do not change.  *choice_out (may be NULL) receives the waves per tile chosen, 0
  * for the direct kernel.  Overwrites the geometry's scratch (no evaluation

@@ -299,7 +299,7 @@ struct qbx_geom_s {
     std::vector<Group> m2l_groups;
     int m2l_Pmax = 0;
     int m2l_nw = 1;                                // waves per M2L tile (0 = direct kernel)
-    int m2l_nw_default = 1;                        // the common row-block count
+    int m2l_nw_default = 1;                        // the rule's choice
     long long total_vy = 0;       // sum over V-list positions of (2 P_l + 1)
     std::vector<int32_t> near_start, near_idx, wf_start, wf_idx;   // host copies
     // M2QBXL work: (leaf, far W) pairs, their output rows and per-leaf ranges
@@ -534,15 +534,19 @@ qbx_status upload(qbx_geom_s *G)
         i = j;
     }
     {
-        // waves per M2L tile: the row-block count of most V pairs, so that
-        // those tiles have one row block per wave
+        // Waves per M2L tile, by the row-block count of most V pairs: 8 (two a
+        // SIMD), or 4 for tables of at most 4 row blocks.  The waves share the
+        // row blocks out among themselves, and with a count that is no
+        // multiple of 4 one SIMD has a wave more than the rest: 9 row blocks
+        // (orders 64-71), four densities of the 32768-node star, 363 us with 9
+        // waves, 310 with 8, 329 with 6, 351 with 4; 200000 nodes 519, 447, 474
+        // and 510; 7 row blocks (orders 54), 110000 nodes 224 with 7, 206 with 8.
         std::vector<long long> cnt(64, 0);
         for (const auto &grp : G->m2l_groups) {
             int nr = (2 * pl.P[grp.key / 40] + 1 + 15) / 16;
             cnt[std::min(nr, 63)] += grp.count;
         }
-        G->m2l_nw = (int)(std::max_element(cnt.begin(), cnt.end()) - cnt.begin());
-        G->m2l_nw = std::max(1, std::min(G->m2l_nw, 16));
+        G->m2l_nw = std::max_element(cnt.begin(), cnt.end()) - cnt.begin() <= 4 ? 4 : 8;
         G->m2l_nw_default = G->m2l_nw;
     }
     g.vpair_sorted = ar.upload(vpos);
@@ -590,6 +594,11 @@ qbx_status upload(qbx_geom_s *G)
                     }
                 }
         }
+        std::vector<int> by(NR);
+        std::iota(by.begin(), by.end(), 0);
+        auto len = [&](int rb) { return rblk[first + rb].k1 - rblk[first + rb].k0; };
+        std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return len(a) > len(b); });
+        for (int i = 0; i < NR; ++i) rblk[first + i].nth = by[i];
         return first;
     };
     if (!pl.opt.direct) {
@@ -2324,7 +2333,7 @@ qbx_status qbx_geom_autotune(qbx_geom G, int32_t n_dens, int32_t *choice_out)
     // Whole evaluations with zero densities, timed with HIP events on the
     // context's stream: the M2L configuration that makes the evaluation
     // fastest in context (caches and the overlapped side stream included).
-    // Candidates: the common row-block count, about half of it, and the
+    // Candidates: the default wave count, about half of it, and the
     // direct-load kernel (0).  They compute the same sums in the same order.
     const Plan &pl = G->pl;
     size_t ns = sizeof(cd) * (size_t)n_dens * std::max<int64_t>(pl.ns, 1);

@@ -390,7 +390,7 @@ __device__ __forceinline__ cd mul_ipow(cd z, int e)
 
 __device__ __forceinline__ RowBlk load_rblk(const DevGeom &g, int i)
 {
-    return RowBlk{g.rblk[i].off, g.rblk[i].k0, g.rblk[i].k1, 0};
+    return RowBlk{g.rblk[i].off, g.rblk[i].k0, g.rblk[i].k1, g.rblk[i].nth};
 }
 
 __device__ __forceinline__ void tb_load(const cd *Arow, int kb, int kb1, const cd *bs, bool bvalid,
@@ -473,8 +473,7 @@ __device__ __forceinline__ void trans_block(const cd *Arow, int kb0, int kb1, co
     cplx3_done(y, yr, yi);
 }
 
-// M2L: one workgroup per 16-column tile, nw waves over its row blocks
-// (rb = wave, wave + nw, ...).  The tile's columns (the source boxes'
+// M2L: one workgroup per 16-column tile, nw waves over its row blocks.  The tile's columns (the source boxes'
 // multipoles) are staged once in LDS through host-precomputed offsets and
 // serve every row block; table fragments stream from memory with the next
 // TB_U k-blocks in flight.  Workgroups run in XCD-contiguous order so that the
@@ -484,14 +483,16 @@ constexpr int M2L_XS = 17;    // LDS row stride of the staged columns (padded)
 __device__ __forceinline__ void m2l_mfma_body(const DevGeom &g, int nd, const M2LTile *tiles, const cd *mp, cd *vy, BlockId bid)
 {
     extern __shared__ double lds_raw[];
+    __shared__ int next[1];                     // the next row block to take
     cd *X = reinterpret_cast<cd *>(lds_raw);    // [4 NK][M2L_XS]
     M2LTile t = tiles[xcd_contiguous(bid.x, bid.nx)];
     int l = t.lo / 40;
     int P = g.Plev[l], n = 2 * P + 1;
     int NK = (n + 3) / 4, NR = (n + 15) / 16;
     int nw = blockDim.x >> 6;
-    int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int bk = lane >> 4, bc = lane & 15;
+    if (threadIdx.x == 0) next[0] = nw;
     {
         // blockDim/16 threads per column, consecutive k per column
         int tpc = blockDim.x >> 4;
@@ -508,8 +509,12 @@ __device__ __forceinline__ void m2l_mfma_body(const DevGeom &g, int nd, const M2
             X[k * M2L_XS + sc] = (col && k < n) ? mul_ipow(col[k], rot * (k - P)) : mk(0.0, 0.0);
     }
     __syncthreads();
+    // The waves take the row blocks longest first, each the next one when it is
+    // done: the blocks about order 0 keep nearly twice the others' k-blocks.
+    // (Which wave sums a block changes nothing in it.)
     const auto *rbd = g.rblk + g.m2l_rb0[t.lo];
-    for (int rb = wave; rb < NR; rb += nw) {
+    for (int i = wave; i < NR;) {
+        const int rb = rbd[i].nth;
         const int k0 = rbd[rb].k0, NB = rbd[rb].k1 - k0;    // kept blocks of the row block (at least one)
         const cd *Ab = g.m2l_mf + (long long)rbd[rb].off * 64 + lane;
         const cd *Xb = X + (k0 * 4 + bk) * M2L_XS + bc;
@@ -547,11 +552,14 @@ __device__ __forceinline__ void m2l_mfma_body(const DevGeom &g, int nd, const M2
             int col = t.col0 + bc;
             cd *o = vy + g.m2l_dst[t.pair_start + col / nd] * nd + (long long)(col % nd) * n;
             int rot = g.m2l_rot[t.pair_start + col / nd];
-            for (int i = 0; i < 4; ++i) {
-                int row = rb * 16 + 4 * i + bk;
-                if (row < n) o[row] = mul_ipow(mk(yr[i], yi[i]), rot * (row - P));
+            for (int e = 0; e < 4; ++e) {
+                int row = rb * 16 + 4 * e + bk;
+                if (row < n) o[row] = mul_ipow(mk(yr[e], yi[e]), rot * (row - P));
             }
         }
+        int got = 0;
+        if (lane == 0) got = atomicAdd(next, 1);
+        i = __builtin_amdgcn_readfirstlane(got);
     }
 }
 

@@ -28,7 +28,8 @@ namespace qbx {
 // L2L 93 to 81; four densities M2L 464 to 379, M2M 192 to 118, L2L 269 to
 // 214; 32 curves of 512-16384 nodes, four densities, 6.63 to 5.35 ms in all.
 struct RowBlk {
-    int off, k0, k1, pad;
+    int off, k0, k1;
+    int nth;        // of the i-th row block of a table: the row block with the i-th most blocks
 };
 
 // All pointers are device pointers.  Points are in tree (Morton) order.
