@@ -72,6 +72,19 @@ __host__ __device__ __forceinline__ int miller_start(double x, int N)
     return k;
 }
 
+// The start where all values up to M are summed: the same product down to
+// 1e-18 and no cap, as what is left out counts by itself and not squared.
+__host__ __device__ __forceinline__ int miller_start_sum(double x, int N)
+{
+    int k = (int)ceil(x > (double)N ? x : (double)N);
+    double bound = 1.0;
+    while (bound > 1e-18) {
+        bound *= x / (2.0 * (k + 1.0) - x);
+        ++k;
+    }
+    return k;
+}
+
 // J_n(x), n = 0..N, written to out[n * stride].  x >= 0.
 __device__ inline void besselj_seq(double x, int N, double *out, long long stride)
 {

@@ -1860,57 +1860,72 @@ __global__ void __launch_bounds__(L2Q_THREADS) k_l2qbxl(DevGeom g, int nd, const
 
 // ---------------------------------------------------------------------------
 // QBX evaluation at associated targets: u = sum_{|l|<=p} alpha_l J_l(w rho) e^{-i l theta}.
-// Miller's recurrence runs downward and the series is summed on the fly.
+// One lane per target.  Miller's recurrence goes to LDS first, normalised by
+// J_0 + 2 (J_2 + J_4 + ...) = 1, so that the sum over orders has no chain but
+// the phase's and its coefficient loads go out together; with the recurrence
+// and the sum in one loop every order waited for its own two loads, and the
+// library's j0 and j1 were as long as both.  With recurrence and library
+// in one loop: 19 us for 512 targets, 15 for 32768 (p = 14), 39 for
+// four densities of them, 25 for 200000 FP64 sources; now 9.6,
+// 10.6, 21.3, 24.6.
 // ---------------------------------------------------------------------------
+constexpr int EVAL_THREADS = 64;   // few targets then still reach every CU
+
+size_t eval_lds_bytes(int p) { return sizeof(double) * EVAL_THREADS * (size_t)(p + 1); }
+
 __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd *coef, cd *u, BlockId bid)
 {
-    int m = bid.x * blockDim.x + threadIdx.x;
+    extern __shared__ double lds_raw[];
+    int m = bid.x * EVAL_THREADS + threadIdx.x;
     if (m >= g.nt) return;
     int i = g.tgt_cs[m];
     if (i < 0) return;
-    int p = g.p;
+    const int p = g.p, nc = g.nc;
     long long nq = 2 * p + 1;
     double dx = g.tx[m] - g.cx[i], dy = g.ty[m] - g.cy[i];
     double rho = sqrt(dx * dx + dy * dy);
     double x = g.omega * rho;
-    cd v = rho > 0.0 ? mk(dx / rho, dy / rho) : mk(1.0, 0.0);    // e^{i theta}
+    cd v = rho > 0.0 ? mk(dx / rho, -dy / rho) : mk(1.0, 0.0);   // e^{-i theta}
     long long o = g.tgt_out ? (long long)g.tgt_out[m] : (long long)m;
-    for (int d = 0; d < nd; ++d) {
-        const cd *a = coef + (long long)d * nq * g.nc + i;
-        cd a0 = a[(long long)p * g.nc];
-        if (x == 0.0) {
-            u[(long long)d * g.u_stride + o] = a0;
-            continue;
-        }
-        int M = miller_start(x, p);
+    double *J = lds_raw + threadIdx.x;
+    double s = 1.0;
+    int top = 0;                                                 // at rho = 0 only l = 0 counts
+    J[0] = 1.0;
+    if (x != 0.0) {
+        top = p;
         double inv = 2.0 / x;
-        double fp1 = 0.0, f = 1e-280, f1 = 0.0;
-        cd S = mk(0.0, 0.0);
-        cd ep = unit_ipow(conj(v), p);  // e^{-i n theta} at n = p, stepped down with n
-        for (int n = M; n > 0; --n) {
-            if (n <= p) {
-                cd t = a[(long long)(p + n) * g.nc] * ep;
-                cd tm = a[(long long)(p - n) * g.nc] * conj(ep);
-                if (n & 1) tm = neg(tm);
-                S = S + f * (t + tm);
-                ep = ep * v;
-            }
-            if (n == 1) f1 = f;
+        double fp1 = 0.0, f = 1e-280, sum = 0.0;
+        for (int n = miller_start_sum(x, p); n > 0; --n) {
+            if (n <= p) J[n * EVAL_THREADS] = f;
+            if (!(n & 1)) sum += f;
             double fm = fma(n * inv, f, -fp1);
             fp1 = f;
             f = fm;
             if (fabs(f) > 1e250) {
-                f *= 1e-250; fp1 *= 1e-250; f1 *= 1e-250;
-                S = 1e-250 * S;
+                f *= 1e-250; fp1 *= 1e-250; sum *= 1e-250;
+                for (int k = n; k <= p; ++k) J[k * EVAL_THREADS] *= 1e-250;
             }
         }
-        double jz = j0(x), jo = j1(x);
-        double s = fabs(jz) >= fabs(jo) ? jz / f : jo / f1;
-        u[(long long)d * g.u_stride + o] = s * S + jz * a0;
+        J[0] = f;
+        s = 1.0 / fma(2.0, sum, f);
+    }
+    for (int d = 0; d < nd; ++d) {
+        const cd *a = coef + (long long)d * nq * nc + i + (long long)p * nc;
+        cd S = J[0] * a[0];
+        cd ep = v;                                               // e^{-i n theta}
+#pragma unroll 4
+        for (int n = 1; n <= top; ++n) {
+            cd t = a[(long long)n * nc] * ep;
+            cd tm = a[-(long long)n * nc] * conj(ep);
+            if (n & 1) tm = neg(tm);
+            S = S + J[n * EVAL_THREADS] * (t + tm);
+            ep = ep * v;
+        }
+        u[(long long)d * g.u_stride + o] = s * S;
     }
 }
 
-__global__ void k_qbx_eval(DevGeom g, int nd, const cd *coef, cd *u)
+__global__ void __launch_bounds__(EVAL_THREADS) k_qbx_eval(DevGeom g, int nd, const cd *coef, cd *u)
 {
     qbx_eval_body(g, nd, coef, u, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
@@ -2144,7 +2159,7 @@ __global__ void __launch_bounds__(L2Q_THREADS) kf_l2qbxl(const FRec *recs, const
                 (int)r.n64, bid);
 }
 
-__global__ void kf_eval(const FRec *recs, const int *map)
+__global__ void __launch_bounds__(EVAL_THREADS) kf_eval(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
     qbx_eval_body(g, r.nd, CP(const cd *, in0), CP(cd *, out0), bid);
@@ -2493,7 +2508,7 @@ hipError_t launch_l2qbxl(const DevGeom &g, int nd, const int *items, int n, int 
 hipError_t launch_qbx_eval(const DevGeom &g, int nd, const cd *coef, cd *u, hipStream_t s)
 {
     if (!g.nt) return hipSuccess;
-    k_qbx_eval<<<(g.nt + 255) / 256, 256, 0, s>>>(g, nd, coef, u);
+    k_qbx_eval<<<(g.nt + EVAL_THREADS - 1) / EVAL_THREADS, EVAL_THREADS, eval_lds_bytes(g.p), s>>>(g, nd, coef, u);
     QBX_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2737,8 +2752,8 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
         break;
     case FK_EVAL:
         for (const auto &it : items) {
-            long long b = ((long long)it.h->nt + 255) / 256;
-            add(kind, 0, it.r, b, b, 0, 256);
+            long long b = ((long long)it.h->nt + EVAL_THREADS - 1) / EVAL_THREADS;
+            add(kind, 0, it.r, b, b, eval_lds_bytes(it.h->p), EVAL_THREADS);
         }
         break;
     case FK_SMOOTH:

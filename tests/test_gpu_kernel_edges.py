@@ -98,6 +98,47 @@ def test_coefficient_sums_at_variant_edges(ctx, p):
         assert np.array_equal(one[0], u[1])
 
 
+# Evaluation of an expansion from the coefficients that the same call returns:
+# target counts around a wavefront, targets on their centre, close to it and
+# far beyond any disk.  A value of J_n with its share of the normalising sum is
+# within 7e-15 of max(|J_n|, its decaying bound) below x = 30, the phase's
+# powers add 2 roundings an order: 2e-14 of the sum of moduli; at x in the
+# hundreds the recurrence rounds at every order, x 1.1e-16 more.
+@pytest.mark.parametrize("p,nt", [(0, 1), (1, 63), (14, 65), (40, 130)])
+def test_expansion_evaluation_edges(ctx, p, nt):
+    mp = pytest.importorskip("mpmath")
+    from paper_1602_05301_amd import qbx
+    r = np.random.default_rng(100 + p)
+    omega, ns = 3.0, 5
+    cx, cy = np.array([0.0, 0.5, -1.0]), np.array([0.0, 0.25, 2.0])
+    ang = r.uniform(0, 2 * np.pi, ns)
+    pts = inputs.Points(9 * np.cos(ang), 9 * np.sin(ang), np.ones(ns), np.cos(ang), np.sin(ang),
+                        np.ones(ns), cx, cy, np.ones(3))
+    tc = (np.arange(nt) % 3).astype(np.int32)
+    rho = 10.0 ** r.uniform(-6, 0.3, nt)
+    rho[::5] = 0.0
+    rho[1::16] = 150.0
+    th = r.uniform(0, 2 * np.pi, nt)
+    tx, ty = cx[tc] + rho * np.cos(th), cy[tc] + rho * np.sin(th)
+    geo = qbx.Geometry(ctx, pts, omega, 1e-10, tx, ty, tc, qbx.options(p=p, direct=True))
+    sig = _dev(r.standard_normal((2, ns)) + 1j * r.standard_normal((2, ns)))
+    u, coef = (a.cpu().numpy() for a in geo.eval(sig, None, coef=True))
+    dx, dy = tx - cx[tc], ty - cy[tc]
+    x = omega * np.hypot(dx, dy)
+    with mp.workdps(30):
+        J = np.array([[float(mp.besselj(n, mp.mpf(float(v)))) for v in x] for n in range(p + 1)])
+    l = np.arange(-p, p + 1)[:, None]
+    Jl = J[abs(l[:, 0])] * np.where((l < 0) & (l % 2 == 1), -1.0, 1.0)
+    E = np.exp(-1j * l * np.arctan2(dy, dx)[None])
+    a = coef.reshape(2, 2 * p + 1, 3)[:, :, tc]
+    ref = (a * Jl * E).sum(1)
+    amp = np.where(x > 1.0, np.sqrt(1.0 / np.maximum(x, 1.0)), 0.0)
+    size = (abs(a) * np.maximum(abs(Jl), np.where(abs(l) <= x, amp, 0.0))).sum(1)
+    err = abs(u - ref) / size
+    print(f"p {p} nt {nt}: {err.max():.2e}", flush=True)
+    assert (err <= 2e-14 + 1.1e-16 * x).all()
+
+
 # Gram-Schmidt products with vector counts around the rows of a block and the
 # rows of the final sums' blocks, lengths around a chunk and past 64 chunks;
 # panel interpolation with panel counts around a block's, and panels too long
