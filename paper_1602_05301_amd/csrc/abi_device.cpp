@@ -715,7 +715,8 @@ qbx_status upload(qbx_geom_s *G)
             lco[i] = G->box_off_h[c];
             int v0 = pl.V_start[c], v1 = pl.V_start[c + 1];
             lvy[i] = v1 > v0 ? G->vy_off_h[v0] : 0;
-            lnv[i] = v1 - v0;
+            // the complement marks a child without X list (l2l_mfma_body)
+            lnv[i] = pl.X_start[c + 1] > pl.X_start[c] ? v1 - v0 : ~(v1 - v0);
         }
         g.m2m_coff = ar.upload(mc);
         g.m2m_poff = ar.upload(mpo);
@@ -1165,12 +1166,6 @@ qbx_status run_pipeline(qbx_geom_s *G, int nd, const cd *ss, const cd *sd, cd *u
     } else {
         qbx_status ts = ensure_tiles(G, nd);
         if (ts != QBX_OK) return ts;
-        if (B.timing || !lane.side) {
-            // in order: the locals are zeroed with the charges (X-list P2L
-            // and L2L both add into them); concurrently, on the side stream
-            STAGE(QBX_STAGE_CHARGES);
-            LAUNCH(QBX_STAGE_CHARGES, G->total_coef, launch_fill_zero(B.loc, (long long)nd * G->total_coef, st));
-        }
         // Fork: the side stream takes the centre J sequences, the X-list P2L,
         // the near field and (once M2M is done) M2QBXL while this stream runs
         // P2M, M2M, M2L and L2L.  With stage profiling on everything stays on
@@ -1185,7 +1180,6 @@ qbx_status run_pipeline(qbx_geom_s *G, int nd, const cd *ss, const cd *sd, cd *u
                 CHK(launch_ctr_rad(g, G->l2q.n, G->crad, G->crad_rows, s1));
                 CHK(launch_x_bas(g, G->n_xpos, G->xbas, s1));
             }
-            CHK(launch_fill_zero(B.loc, (long long)nd * G->total_coef, s1));
             CHK(launch_p2l_x(g, nd, G->xl.d, G->xl.n, G->xl.Pmax, B.qs, B.qd, B.loc, true, s1));
             if (G->n_wpairs > 0) CHK(hipEventRecord(C->ev_x, s1));
             CHK(launch_p2qbxl(g, nd, G->qbx.d, G->qbx.n, B.qs, B.qd, B.coef, true, s1));
@@ -1234,8 +1228,8 @@ qbx_status run_pipeline(qbx_geom_s *G, int nd, const cd *ss, const cd *sd, cd *u
             // V-list sums in list order for every level at once, then L2L
             // from the parent, level by level
             STAGE(QBX_STAGE_L2L);
-            if (pl.nlev > 2) {
-                int nbox = pl.level_start[pl.nlev] - pl.level_start[2];
+            {
+                int nbox = pl.level_start[pl.nlev];
                 LAUNCH(QBX_STAGE_L2L, nbox, launch_down_all(g, nd, nbox, B.vy, B.loc, st));
             }
             for (int L = 3; L < pl.nlev; ++L) {
@@ -1424,12 +1418,6 @@ qbx_status plan_pass(const std::vector<BItem> &B, const QbxLane &L, bool conc, F
             return it.n > 0 && !b.G->rad_ready;
         });
     };
-    auto v_fill = [&]() {
-        return over([](const BItem &b, FItem &it) {
-            it.r.out0 = b.G->loc; it.n = (long long)b.nd * b.G->total_coef;
-            return true;
-        });
-    };
     auto v_x_bas = [&]() {
         return over([](const BItem &b, FItem &it) {
             it.r.out0 = b.G->xbas; it.r.n64 = b.G->n_xpos; it.n = b.G->n_xpos;
@@ -1474,7 +1462,6 @@ qbx_status plan_pass(const std::vector<BItem> &B, const QbxLane &L, bool conc, F
             record(L.ev_fork, 0);
             wait(1, L.ev_fork);
             QQ(stage(FK_CTR_RAD, v_ctr_rad(), 1));
-            QQ(stage(FK_FILL, v_fill(), 1));
             QQ(stage(FK_X_BAS, v_x_bas(), 1));
             QQ(stage(FK_P2L_X, v_p2l_x(), 1));
             record(L.ev_x, 1);
@@ -1516,16 +1503,14 @@ qbx_status plan_pass(const std::vector<BItem> &B, const QbxLane &L, bool conc, F
         if (conc) {
             wait(0, L.ev_x);
         } else {
-            QQ(stage(FK_FILL, v_fill(), 0));
             QQ(stage(FK_X_BAS, v_x_bas(), 0));
             QQ(stage(FK_P2L_X, v_p2l_x(), 0));
         }
         QQ(stage(FK_DOWN, over([](const BItem &b, FItem &it) {
                      const Plan &pl = b.G->pl;
-                     if (pl.nlev <= 2) return false;
-                     // level 2 only: the fused L2L levels sum their own V-list rows
-                     it.r.i0 = 2; it.r.in0 = b.G->vy; it.r.out0 = b.G->loc;
-                     it.n = pl.level_start[3] - pl.level_start[2];
+                     // up to level 2: the fused L2L levels sum their own V-list rows
+                     it.r.i0 = 0; it.r.in0 = b.G->vy; it.r.out0 = b.G->loc;
+                     it.n = pl.level_start[std::min(3, (int)pl.nlev)];
                      return it.n > 0;
                  }), 0));
         for (int Lv = 3; Lv < maxlev; ++Lv)

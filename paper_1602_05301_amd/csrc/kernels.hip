@@ -21,20 +21,8 @@
 namespace qbx {
 
 // ---------------------------------------------------------------------------
-// Utilities
+// Charges
 // ---------------------------------------------------------------------------
-
-__device__ __forceinline__ void fill_zero_body(cd *p, long long n, BlockId bid)
-{
-    long long i = (long long)bid.x * blockDim.x + threadIdx.x;
-    long long step = (long long)bid.nx * blockDim.x;
-    for (; i < n; i += step) p[i] = mk(0.0, 0.0);
-}
-
-__global__ void k_fill_zero(cd *p, long long n)
-{
-    fill_zero_body(p, n, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
-}
 
 // qS[d][j] = (i/4) w_j sigma_S[d][perm[j]] (sorted source order); same for qD.
 __device__ __forceinline__ void charges_body(const DevGeom &g, int nd, const cd *sig_s, const cd *sig_d, cd *qs, cd *qd, BlockId bid)
@@ -355,23 +343,26 @@ __device__ __forceinline__ void down_body(const DevGeom &g, int nd, int l, const
     int P = g.Plev[g.blev[b]], n = 2 * P + 1;
     cd *out = loc + g.box_off[b] * nd;
     int v0 = g.V_start[b], nv = g.V_start[b + 1] - v0;
-    if (nv == 0) return;
+    const bool hasx = g.X_start[b + 1] > g.X_start[b];
+    if (nv == 0 && hasx) return;
     // the box's V-list rows follow each other, n * nd apart
     const cd *vr = vy + g.vy_off[v0] * nd;
     long long vs = (long long)n * nd;
     for (int i = threadIdx.x; i < nd * n; i += blockDim.x) {
-        cd acc = out[i];
+        cd acc = hasx ? out[i] : mk(0.0, 0.0);
 #pragma unroll 4
         for (int v = 0; v < nv; ++v) acc = acc + vr[v * vs + i];
         out[i] = acc;
     }
 }
 
-// V-list sums of every box from level 2 on (one block of 64 lanes per
-// density per box)
+// V-list sums of every box (one block of 64 lanes per density per box).  A box
+// with an X list starts from what that list's kernel wrote, any other from
+// zero, so nothing clears the locals first (a fill of 30 MB on the star of
+// 32768 nodes).
 __global__ void __launch_bounds__(256) k_down_all(DevGeom g, int nd, const cd *vy, cd *loc)
 {
-    down_body(g, nd, 2, vy, loc, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
+    down_body(g, nd, 0, vy, loc, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
 // Part of one 16x16 output block of a scaled translation on FP64 MFMA: rows
@@ -821,9 +812,14 @@ __device__ __forceinline__ void l2l_mfma_body(const DevGeom &g, int nd, int L, c
     __syncthreads();
     if (!own) return;
     // V-list rows of the child follow each other, nc * nd apart
-    // vy null: the V-list rows are already in loc
+    // vy null: the V-list rows are already in loc.  Else a count below zero
+    // (its complement) marks a child without X list: its loc is not written yet.
     const cd *vr = vy ? vy + g.l2l_vy0[pos] * nd + dr : nullptr;
     int nv = vy ? g.l2l_nv[pos] : 0;
+    if (nv < 0) {
+        nv = ~nv;
+        acc = mk(0.0, 0.0);
+    }
     long long vs = (long long)nc * nd;
 #pragma unroll 4
     for (int v = 0; v < nv; ++v) acc = acc + vr[v * vs];
@@ -879,9 +875,14 @@ __device__ __forceinline__ void l2l_mfma32_body(const DevGeom &g, int nd, int L,
     for (int i = 0; i < 4; ++i) { part[w][lane][i] = (double)yr[i]; part[w][lane][4 + i] = (double)yi[i]; }
     __syncthreads();
     if (!own) return;
-    // vy null: the V-list rows are already in loc
+    // vy null: the V-list rows are already in loc.  Else a count below zero
+    // (its complement) marks a child without X list: its loc is not written yet.
     const cd *vr = vy ? vy + g.l2l_vy0[pos] * nd + dr : nullptr;
     int nv = vy ? g.l2l_nv[pos] : 0;
+    if (nv < 0) {
+        nv = ~nv;
+        acc = mk(0.0, 0.0);
+    }
     long long vs = (long long)nc * nd;
 #pragma unroll 4
     for (int v = 0; v < nv; ++v) acc = acc + vr[v * vs];
@@ -965,6 +966,8 @@ __device__ __forceinline__ void p2l_x_body(const DevGeom &g, const int *list, co
     double mx = g.bcx[b], my = g.bcy[b], hw = 0.5 * g.omega;
     cd *out = loc + g.box_off[b] * ND;
     int q0 = g.xsrc_start[bid.x], total = g.xsrc_start[bid.x + 1] - q0;
+    if (total == 0)
+        for (int i = tid; i < np * ND; i += blockDim.x) out[i] = mk(0.0, 0.0);
     int nseg = (P + 2 + PT_SEG - 1) / PT_SEG;
     for (int f0 = 0; f0 < total; f0 += CH) {
         int cnt = min(CH, total - f0);
@@ -2029,13 +2032,6 @@ __device__ __forceinline__ FRec fused_rec(const FRec *recs, const int *map, Bloc
 
 #define CP(T, x) ((T)(r.x))
 
-__global__ void kf_fill(const FRec *recs, const int *map)
-{
-    FUSED_BEGIN
-    (void)g;
-    fill_zero_body(CP(cd *, out0), r.n64, bid);
-}
-
 __global__ void kf_charges(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
@@ -2182,15 +2178,6 @@ __global__ void __launch_bounds__(64) kf_smooth(const FRec *recs, const int *map
         hipError_t e_ = hipGetLastError();                   \
         if (e_ != hipSuccess) return e_;                     \
     } while (0)
-
-hipError_t launch_fill_zero(cd *p, long long n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    int blocks = (int)std::min<long long>((n + 255) / 256, 4096);
-    k_fill_zero<<<blocks, 256, 0, s>>>(p, n);
-    QBX_LAUNCH_CHECK();
-    return hipSuccess;
-}
 
 hipError_t launch_charges(const DevGeom &g, int nd, const cd *ss, const cd *sd, cd *qs, cd *qd,
                           hipStream_t s)
@@ -2534,7 +2521,6 @@ hipError_t launch_coef_out(const DevGeom &g, int nd, const cd *coef, cd *out, hi
 // ---------------------------------------------------------------------------
 // Fused-launch planning.  Record fields per stage, besides g and nd (item
 // sizes n, P, aux in brackets):
-//   FILL           out0 = array, n64 = elements                      [n = elements]
 //   CHARGES        in0 = sigma_S, in1 = sigma_D, out0 = qS, out1 = qD
 //   SRC_RAD        i0 = rows, out0 = J table                         [n = P2M leaves]
 //   CTR_RAD        i0 = rows, out0 = J table                         [n = L2QBXL items]
@@ -2607,14 +2593,6 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
         rows.push_back({k, v, threads, r, blocks, lds});
     };
     switch (kind) {
-    case FK_FILL:
-        for (const auto &it : items) {
-            FRec r = it.r;
-            r.n64 = it.n;
-            long long b = std::min<long long>((it.n + 255) / 256, 1024);
-            add(kind, 0, r, b, b, 0, 256);
-        }
-        break;
     case FK_CHARGES:
         for (const auto &it : items) {
             long long b = ((long long)it.r.nd * it.h->ns + 255) / 256;
@@ -2791,7 +2769,6 @@ hipError_t fused_launch(const FLaunch &L, const unsigned char *dev, hipStream_t 
     size_t lds = L.lds;
 #define FL(...) __VA_ARGS__<<<grid, block, lds, s>>>(recs, map)
     switch (L.kind) {
-    case FK_FILL: FL(kf_fill); break;
     case FK_CHARGES: FL(kf_charges); break;
     case FK_SRC_BAS: FL(kf_src_bas); break;
     case FK_X_BAS: FL(kf_x_bas); break;

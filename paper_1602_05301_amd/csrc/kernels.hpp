@@ -91,7 +91,8 @@ struct DevGeom {
     // per position of the M2M parent list: children's box_off by quadrant
     // (-1 = none) and the parent's; per position of the L2L child list: the
     // parent's and the child's box_off, the vy row of its first V-list entry
-    // and the entry count (the entries' rows follow each other)
+    // and the entry count (the entries' rows follow each other), as its
+    // complement for a child without X list
     const QBX_G long long *m2m_coff, *m2m_poff;
     const QBX_G long long *l2l_poff, *l2l_coff, *l2l_vy0;
     const QBX_G int *l2l_nv;
@@ -153,7 +154,7 @@ struct FRec {
 };
 
 enum FKind {
-    FK_FILL, FK_CHARGES, FK_SRC_BAS, FK_X_BAS, FK_CTR_RAD, FK_P2M, FK_M2M, FK_M2L, FK_DOWN, FK_L2L, FK_P2L_X,
+    FK_CHARGES, FK_SRC_BAS, FK_X_BAS, FK_CTR_RAD, FK_P2M, FK_M2M, FK_M2L, FK_DOWN, FK_L2L, FK_P2L_X,
     FK_P2QBXL, FK_P2QBXL_DIRECT, FK_M2QBXL, FK_WSUM, FK_L2QBXL, FK_EVAL, FK_SMOOTH,
     // chosen by the planner
     FK_M2L_DIRECT, FK_M2L32, FK_L2L32, FK_P2L_XC
@@ -189,7 +190,6 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
 // Launches fb.launches[i] with its records at dev (the device copy of fb.bytes).
 hipError_t fused_launch(const FLaunch &L, const unsigned char *dev, hipStream_t s);
 
-hipError_t launch_fill_zero(cd *p, long long n, hipStream_t s);
 hipError_t launch_charges(const DevGeom &g, int nd, const cd *ss, const cd *sd, cd *qs, cd *qd,
                           hipStream_t s);
 // The geometry-only bases of P2M (into sbas, g.srow per source) and of the

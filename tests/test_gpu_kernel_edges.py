@@ -139,6 +139,33 @@ def test_expansion_evaluation_edges(ctx, p, nt):
     assert (err <= 2e-14 + 1.1e-16 * x).all()
 
 
+# The locals start from what the X lists' kernel wrote or from nothing: what an
+# earlier evaluation left there (here NaN everywhere) has no part in the next
+# one.  Alone and batched, one and three densities, FP64 and FP32 far field, a
+# tree of a single box, and one on the path that allocates nothing.
+@pytest.mark.parametrize("nseg,far32", [(2, False), (60, False), (60, True)])
+def test_evaluation_ignores_earlier_locals(ctx, nseg, far32):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(nseg, 16, lobes=5, amp=0.45)
+    geo = qbx.Geometry(ctx, g, 20.0, 1e-6, g.sx, g.sy, np.arange(g.n, dtype=np.int32),
+                       qbx.options(p=6, far_fp32=far32))
+    for nd in (1, 3):
+        ss, sd = (_dev(a) for a in _densities(g, nd, 77))
+        bad = torch.full_like(ss, float("nan"))
+        ref = geo.eval(ss, sd)
+        out = [torch.empty_like(ref) for _ in range(3)]
+        geo.eval(bad, bad)
+        geo.eval(ss, sd, u=out[0])
+        ctx.eval_batch([geo], [bad], [bad], [out[1]])
+        ctx.eval_batch([geo], [ss], [sd], [out[1]])
+        geo.eval_noalloc(bad, bad, out[2])
+        geo.eval_noalloc(ss, sd, out[2])
+        torch.cuda.synchronize()
+        assert torch.isfinite(torch.view_as_real(ref)).all()
+        for o in out:
+            assert torch.equal(torch.view_as_real(o), torch.view_as_real(ref))
+
+
 # Gram-Schmidt products with vector counts around the rows of a block and the
 # rows of the final sums' blocks, lengths around a chunk and past 64 chunks;
 # panel interpolation with panel counts around a block's, and panels too long
