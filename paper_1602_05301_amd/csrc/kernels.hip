@@ -10,7 +10,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstring>
 #include <vector>
 
@@ -732,8 +731,8 @@ __device__ __forceinline__ cd tb_sum(const double (*part)[64][9], int nw, int r,
 // (w % 4) matrix over part w / 4 of its k-blocks (M2M_KS parts); the partial
 // blocks are summed in wave order.  One part (four waves, 18 KiB of LDS) lets
 // the workgroups of a level find room beside the near field on the other
-// stream: the step 0.452 to 0.446 ms, though each level alone is slower than
-// with two parts (M2M in order 101 against 105 us).
+// stream: with two parts 32768 nodes take 381 us a pass against 353, 200000
+// nodes 1888 against 1768.
 constexpr int M2M_KS = 1;
 
 __device__ __forceinline__ void m2m_mfma_body(const DevGeom &g, int nd, int l, const TTile *tiles, const int *plist, cd *mp, BlockId bid)
@@ -1153,19 +1152,6 @@ __global__ void __launch_bounds__(64) k_p2l_xc(DevGeom g, const int *list, const
     p2l_xc_body<ND>(g, list, qs, qd, loc, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
-// The capped form beside the other stream: the grid walks the boxes back and
-// forth, as the near field does.  (Its loop keeps more registers live, 96
-// against 64 VGPRs, so launches that are not capped take the plain form.)
-template <int ND>
-__global__ void __launch_bounds__(64) k_p2l_xc_capped(DevGeom g, int n, const int *list, const cd *qs, const cd *qd, cd *loc)
-{
-    int G = gridDim.x;
-    for (int r = 0; r * G < n; ++r) {
-        int b = r * G + ((r & 1) ? G - 1 - (int)blockIdx.x : (int)blockIdx.x);
-        if (b < n) p2l_xc_body<ND>(g, list, qs, qd, loc, BlockId{b, (int)blockIdx.y, n});
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Stage 3: P2QBXL.  alpha_l(c) += qS O_l(s-c) + qD (w/2)(nu O_{l-1} - conj(nu) O_{l+1}).
 // With z = s - c = (x/omega) u, |u| = 1, O_{+-m} = (+-1)^m H_m u^{+-m} and
@@ -1364,22 +1350,6 @@ template <int PB>
 __global__ void __launch_bounds__(P2Q_THREADS) k_p2qbxl(DevGeom g, int nd, const int *items, const cd *qs, const cd *qd, cd *coef)
 {
     p2qbxl_body<PB>(g, nd, items, qs, qd, coef, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
-}
-
-// A capped grid: workgroup b takes items b, 2G-1-b, 2G+b, ... (G = gridDim.x),
-// back and forth over the list, which the host sorts by decreasing work, so
-// the workgroups' totals stay close.  Each item's body begins and ends its LDS
-// use behind barriers, so items follow each other in a workgroup safely.  (The
-// loop costs registers, 231 against 228 VGPRs with a little scratch, so
-// launches that are not capped take the plain form.)
-template <int PB>
-__global__ void __launch_bounds__(P2Q_THREADS) k_p2qbxl_capped(DevGeom g, int nd, int n_items, const int *items, const cd *qs, const cd *qd, cd *coef)
-{
-    int G = gridDim.x;
-    for (int r = 0; r * G < n_items; ++r) {
-        int b = r * G + ((r & 1) ? G - 1 - (int)blockIdx.x : (int)blockIdx.x);
-        if (b < n_items) p2qbxl_body<PB>(g, nd, items, qs, qd, coef, BlockId{b, 0, n_items});
-    }
 }
 
 // Direct mode: all sources to every centre (Sec. 3.2, oversampled coefficient sum).
@@ -1692,7 +1662,9 @@ __global__ void k_wsum(DevGeom g, int nd, const int *leaf_list, const int *leaf_
 // The n range of a block is the one whose terms count (l2q_rng): in a box
 // small against the wavelength an order l > 0 takes the locals of k from about
 // l on, l < 0 those up to about l, and only the block about l = 0 both.
-// L2QBXL_FIGURES
+// Bound by FP64 issue and the LDS reads that feed it.  With every n and range
+// tests in the loop: 62 us for 32768 nodes (p = 14), 204 for four densities,
+// 321 for 200000 nodes (p = 9); now 54, 172 and 253.
 // ---------------------------------------------------------------------------
 constexpr int L2Q_THREADS = 256;   // lanes per item: 16 slots x 4 l-blocks x 4 quarters
 constexpr int L2Q_PAD = 16;        // zeros around a run's locals and a centre's J_n
@@ -2234,20 +2206,6 @@ hipError_t launch_p2m(const DevGeom &g, int nd, const int *list, int n, int Pmax
     return hipSuccess;
 }
 
-// Compute units of the current device (cached per device).
-static int device_cu_count()
-{
-    static std::atomic<int> cus[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cus[dev].load(std::memory_order_relaxed);
-    if (n <= 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cus[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 hipError_t launch_m2m_mfma(const DevGeom &g, int nd, int l, const TTile *tiles, int ntiles,
                            int nrb, const int *plist, cd *mp, hipStream_t s)
 {
@@ -2319,37 +2277,15 @@ hipError_t launch_down_all(const DevGeom &g, int nd, int nbox, const cd *vy, cd 
     return hipSuccess;
 }
 
-// The X-list P2L beside the other stream, like the near field after it, is
-// capped so that the first M2M levels and P2M find room: 4 waves per CU (one
-// per SIMD), while the launch has at most 32 waves per CU (the star: 2466
-// boxes x 2 runs of orders, 19 per CU).  Step 0.446 to 0.440 ms; 2 waves per
-// CU: 0.475 ms.
-#ifndef XC_WAVES_PER_CU
-#define XC_WAVES_PER_CU 4
-#endif
-constexpr int XC_CAP_WAVES_PER_CU = 32;
-
 hipError_t launch_p2l_x(const DevGeom &g, int nd, const int *list, int n, int Pmax, const cd *qs,
-                        const cd *qd, cd *loc, bool beside, hipStream_t s)
+                        const cd *qd, cd *loc, hipStream_t s)
 {
     if (!n) return hipSuccess;
     if (nd < 1 || nd > 4) return hipErrorInvalidValue;
     if (g.xbas) {
         // rows kept with the geometry (launch_x_bas)
-        int runs = order_runs(Pmax), cus = device_cu_count();
         size_t lds = p2l_xc_lds_bytes(nd);
-        if (beside && XC_WAVES_PER_CU > 0 && (long long)n * runs <= (long long)XC_CAP_WAVES_PER_CU * cus) {
-            dim3 grid(std::min(n, std::max(1, XC_WAVES_PER_CU * cus / runs)), runs);
-            switch (nd) {
-            case 1: k_p2l_xc_capped<1><<<grid, 64, lds, s>>>(g, n, list, qs, qd, loc); break;
-            case 2: k_p2l_xc_capped<2><<<grid, 64, lds, s>>>(g, n, list, qs, qd, loc); break;
-            case 3: k_p2l_xc_capped<3><<<grid, 64, lds, s>>>(g, n, list, qs, qd, loc); break;
-            default: k_p2l_xc_capped<4><<<grid, 64, lds, s>>>(g, n, list, qs, qd, loc); break;
-            }
-            QBX_LAUNCH_CHECK();
-            return hipSuccess;
-        }
-        dim3 grid(n, runs);
+        dim3 grid(n, order_runs(Pmax));
         switch (nd) {
         case 1: k_p2l_xc<1><<<grid, 64, lds, s>>>(g, list, qs, qd, loc); break;
         case 2: k_p2l_xc<2><<<grid, 64, lds, s>>>(g, list, qs, qd, loc); break;
@@ -2372,50 +2308,33 @@ hipError_t launch_p2l_x(const DevGeom &g, int nd, const int *list, int n, int Pm
     return hipSuccess;
 }
 
-// Workgroups per CU of the near-field launch when it runs beside the other
-// stream.  At 228 VGPRs a lane two of its waves fill a SIMD's registers; with
-// one workgroup per item the near field takes every CU, and the latency-bound
-// M2M levels of the other stream wait for it to drain before their workgroups
-// get one.  Two workgroups per CU (one wave per SIMD) leave room for them.
-// Measured on the 32768-node star: 0.470 ms a step against 0.487-0.490 with
-// one workgroup per item (1: 0.522, 3: 0.495, 4: 0.486).  Alone on the
-// device (in order) the launch takes one workgroup per item.
-#ifndef P2Q_WG_PER_CU
-#define P2Q_WG_PER_CU 2
-#endif
-// The cap pays only while the near field is short next to the other
-// stream's chain (the 32768-node star: 3454 items, 13.5 per CU).  With many
-// items per CU, as on the 606k-node multiscale set with leaves of 64, the
-// near field is the longer stream, and capped it becomes the critical path.
-#ifndef P2Q_CAP_ITEMS_PER_CU
-#define P2Q_CAP_ITEMS_PER_CU 16
-#endif
-
+// One workgroup per item and per (box, run of orders), also where these launches
+// share the device with the other stream's chain.  Grids of two workgroups per
+// CU that walked their items (four waves per CU for the X lists) left the M2M
+// levels more room, which paid while an item took half as long again: a pass
+// over 32768 nodes 384 us with them, 367 with three and 361 with four near-field
+// workgroups per CU, 358 with eight waves of the X lists as well, 353 with one
+// per item.
 
 template <int PB>
 static hipError_t p2qbxl_dispatch(const DevGeom &g, int nd, const int *items, int n, const cd *qs,
-                                  const cd *qd, cd *coef, bool beside, hipStream_t s)
+                                  const cd *qd, cd *coef, hipStream_t s)
 {
-    int cus = device_cu_count();
-    if (beside && P2Q_WG_PER_CU > 0 && n <= P2Q_CAP_ITEMS_PER_CU * cus)
-        k_p2qbxl_capped<PB><<<std::min(n, P2Q_WG_PER_CU * cus), P2Q_THREADS, p2qbxl_lds_bytes(), s>>>(
-            g, nd, n, items, qs, qd, coef);
-    else
-        k_p2qbxl<PB><<<n, P2Q_THREADS, p2qbxl_lds_bytes(), s>>>(g, nd, items, qs, qd, coef);
+    k_p2qbxl<PB><<<n, P2Q_THREADS, p2qbxl_lds_bytes(), s>>>(g, nd, items, qs, qd, coef);
     return hipGetLastError();
 }
 
 hipError_t launch_p2qbxl(const DevGeom &g, int nd, const int *items, int n, const cd *qs,
-                         const cd *qd, cd *coef, bool beside, hipStream_t s)
+                         const cd *qd, cd *coef, hipStream_t s)
 {
     if (!n) return hipSuccess;
-    if (g.p <= 8) return p2qbxl_dispatch<8>(g, nd, items, n, qs, qd, coef, beside, s);
-    if (g.p <= 12) return p2qbxl_dispatch<12>(g, nd, items, n, qs, qd, coef, beside, s);
-    if (g.p <= 14) return p2qbxl_dispatch<14>(g, nd, items, n, qs, qd, coef, beside, s);
-    if (g.p <= 16) return p2qbxl_dispatch<16>(g, nd, items, n, qs, qd, coef, beside, s);
-    if (g.p <= 24) return p2qbxl_dispatch<24>(g, nd, items, n, qs, qd, coef, beside, s);
-    if (g.p <= 32) return p2qbxl_dispatch<32>(g, nd, items, n, qs, qd, coef, beside, s);
-    return p2qbxl_dispatch<40>(g, nd, items, n, qs, qd, coef, beside, s);
+    if (g.p <= 8) return p2qbxl_dispatch<8>(g, nd, items, n, qs, qd, coef, s);
+    if (g.p <= 12) return p2qbxl_dispatch<12>(g, nd, items, n, qs, qd, coef, s);
+    if (g.p <= 14) return p2qbxl_dispatch<14>(g, nd, items, n, qs, qd, coef, s);
+    if (g.p <= 16) return p2qbxl_dispatch<16>(g, nd, items, n, qs, qd, coef, s);
+    if (g.p <= 24) return p2qbxl_dispatch<24>(g, nd, items, n, qs, qd, coef, s);
+    if (g.p <= 32) return p2qbxl_dispatch<32>(g, nd, items, n, qs, qd, coef, s);
+    return p2qbxl_dispatch<40>(g, nd, items, n, qs, qd, coef, s);
 }
 
 // Centres per wave of the direct sum: one when there are few centres (the

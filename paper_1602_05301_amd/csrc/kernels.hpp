@@ -216,20 +216,16 @@ int m2l_staged_pmax();
 // >= 2) in one launch, nd (1-4) densities; launch_l2l_mfma with vy = null
 // then leaves them out of its epilogue.
 hipError_t launch_down_all(const DevGeom &g, int nd, int nbox, const cd *vy, cd *loc, hipStream_t s);
-// X-list P2L into the locals of the listed boxes.  beside: the launch runs
-// concurrently with the other stream's chain (a short launch is then capped
-// so that the chain's launches find room on every CU).
+// X-list P2L into the locals of the listed boxes.
 hipError_t launch_p2l_x(const DevGeom &g, int nd, const int *list, int n, int Pmax, const cd *qs,
-                        const cd *qd, cd *loc, bool beside, hipStream_t s);
+                        const cd *qd, cd *loc, hipStream_t s);
 // P2QBXL: one workgroup of P2Q_THREADS lanes per work item.  An item is
 // four ints {c0, c1, q0, q1}: centres [c0, c1) of one leaf (sorted order) and
 // that leaf's near-list sources qsrc_idx[q0, q1).  The lanes form
 // CG = min(c1 - c0, P2Q_THREADS / 2) centre slots of P2Q_THREADS / CG parts.
 constexpr int P2Q_THREADS = 128;
-// beside: the launch runs concurrently with the other stream's chain (its
-// grid is then capped so that the chain's launches find room on every CU)
 hipError_t launch_p2qbxl(const DevGeom &g, int nd, const int *items, int n, const cd *qs,
-                         const cd *qd, cd *coef, bool beside, hipStream_t s);
+                         const cd *qd, cd *coef, hipStream_t s);
 hipError_t launch_p2qbxl_direct(const DevGeom &g, int nd, const cd *qs, const cd *qd, cd *coef,
                                 hipStream_t s);
 hipError_t launch_m2qbxl(const DevGeom &g, int nd, const int2 *pairs, const long long *pair_off,
