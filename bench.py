@@ -454,6 +454,9 @@ def main(argv=None):
     ms_step = elapsed / args.steps * 1e3
     value = g.n * wl.n_dens * args.steps / elapsed
     def stage_roof(st):
+        # work counts the dense operators; the translations and L2QBXL multiply
+        # only the entries that count, about half, so their rate here is the
+        # operator's, not the matrix cores'
         ms = stages[st][0] / args.steps
         achieved = work[st] / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
         # translations on the FP64 matrix cores; everything else on the FP64 vector ALUs
