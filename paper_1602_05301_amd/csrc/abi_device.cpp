@@ -281,6 +281,12 @@ struct WorkList {
 // Largest (centre, source) pair count a P2QBXL lane is given before its leaf
 // is split over several workgroups (about twice the typical leaf's).
 constexpr long long kP2qLanePairs = 8;
+// Where items of twice that are still 16 per CU, many follow each other on every
+// CU and the few that outlast the rest matter less than each item's staging and
+// reduction: curves with leaves of 64 (110000 nodes) 822 us a pass with 8 and
+// 787 with 16, 200000 nodes 1770 and 1753.  Below, the launch lasts as long as
+// its longest items: 32768 nodes (13 per CU) 353 and 361.
+constexpr long long kP2qManyItems = 16 * 256;
 
 }  // namespace
 
@@ -847,7 +853,7 @@ qbx_status upload(qbx_geom_s *G)
         // them).  An item of CG = min(centres, P2Q_THREADS / 2) slots gives a
         // lane ceil(sources / (P2Q_THREADS / CG)) pairs per pass over its
         // centres; a leaf whose near list would give a lane more than
-        // kP2qLanePairs is split into the fewest groups of consecutive
+        // lane_limit is split into the fewest groups of consecutive
         // centres that stay within it, so that one crowded leaf does not hold
         // its workgroup long after the rest have drained.  Items run in order
         // of decreasing lane work (each centre's result is independent of the
@@ -857,6 +863,20 @@ qbx_status upload(qbx_geom_s *G)
             long long parts = P2Q_THREADS / cg;
             return ((n_s + parts - 1) / parts) * ((n_c + cg - 1) / cg);
         };
+        auto near_sources = [&](int b) {
+            long long n = 0;
+            for (int i = ns[b]; i < ns[b + 1]; ++i) n += pl.src_end[nidx[i]] - pl.src_begin[nidx[i]];
+            return n;
+        };
+        auto groups = [&](int b, long long nsrc, long long limit) {
+            long long nc = pl.ctr_end[b] - pl.ctr_begin[b], ng = 1;
+            while (ng < nc && lane_pairs((nc + ng - 1) / ng, nsrc) > limit) ++ng;
+            return ng;
+        };
+        long long many = 0;
+        for (int b = 0; b < nb && many < kP2qManyItems; ++b)
+            if (pl.leaf[b] && has_ctr(b)) many += groups(b, near_sources(b), 2 * kP2qLanePairs);
+        const long long lane_limit = many < kP2qManyItems ? kP2qLanePairs : 2 * kP2qLanePairs;
         std::vector<int32_t> qidx;
         std::vector<std::array<int32_t, 4>> qitems;
         std::vector<long long> qwork;
@@ -868,8 +888,7 @@ qbx_status upload(qbx_geom_s *G)
             for (int i = ns[b]; i < ns[b + 1]; ++i)
                 for (int j = pl.src_begin[nidx[i]]; j < pl.src_end[nidx[i]]; ++j) qidx.push_back(j);
             int q1 = (int)qidx.size();
-            long long nc = pl.ctr_end[b] - pl.ctr_begin[b], nsrc = q1 - q0, ng = 1;
-            while (ng < nc && lane_pairs((nc + ng - 1) / ng, nsrc) > kP2qLanePairs) ++ng;
+            long long nc = pl.ctr_end[b] - pl.ctr_begin[b], nsrc = q1 - q0, ng = groups(b, nsrc, lane_limit);
             for (long long k = 0; k < ng; ++k) {
                 int a = pl.ctr_begin[b] + (int)(k * nc / ng), e = pl.ctr_begin[b] + (int)((k + 1) * nc / ng);
                 qitems.push_back({a, e, q0, q1});

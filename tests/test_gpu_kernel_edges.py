@@ -166,6 +166,22 @@ def test_evaluation_ignores_earlier_locals(ctx, nseg, far32):
             assert torch.equal(torch.view_as_real(o), torch.view_as_real(ref))
 
 
+# Near-field items on both sides of the rule for larger ones (131072 points in
+# leaves of 64 make some 8000, 8192 points 1000): the FMM against the direct mode at every
+# target.  eps is 1e-8, ten times that in l2.
+@pytest.mark.parametrize("panels,leaf", [(512, 16), (8192, 64)])
+def test_near_field_items_on_both_sides_of_the_rule(ctx, panels, leaf):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(panels, 16, lobes=7, amp=0.3)
+    tc = np.arange(g.n, dtype=np.int32)
+    sig = _dev(_densities(g, 1, 51)[0])
+    u = [qbx.Geometry(ctx, g, 40.0, 1e-8, g.sx, g.sy, tc, qbx.options(p=10, leaf_max=leaf, direct=d)).eval(sig, sig)
+         for d in (False, True)]
+    err = float(torch.linalg.norm(u[0] - u[1]) / torch.linalg.norm(u[1]))
+    print(f"panels {panels} leaf {leaf}: {err:.2e}", flush=True)
+    assert err <= 1e-7
+
+
 # Gram-Schmidt products with vector counts around the rows of a block and the
 # rows of the final sums' blocks, lengths around a chunk and past 64 chunks;
 # panel interpolation with panel counts around a block's, and panels too long
