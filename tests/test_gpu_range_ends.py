@@ -1,0 +1,59 @@
+"""Calls at the ends of the ranges that the kernels take: orders at their LDS
+limits, arguments at the ends of the exponent range, query buffers in any
+order of calls."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1602_05301_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1602_05301_amd import qbx
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return qbx.Context(0)
+
+
+def _dev(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+# H_0 and H_1 at omega 2^k and targets at powers of two from one source at the
+# origin, so that x is exact: at centres (p = 0) and by the smooth rule.  As
+# between the forms of the ordinary range: 4e-15.
+def _hankel_at(ctx, which, bound, k):
+    mp = pytest.importorskip("mpmath")
+    from paper_1602_05301_amd import qbx
+    omega, d = 2.0 ** k, 2.0 ** np.arange(-3, 4)
+    pts = inputs.Points(np.zeros(1), np.zeros(1), np.ones(1), np.ones(1), np.zeros(1), np.full(1, 1e-3),
+                        d, 0.0 * d, 1e-3 * d)
+    tx = d if bound else -d
+    tc = np.arange(d.size, dtype=np.int32) if bound else np.full(d.size, -1, dtype=np.int32)
+    geo = qbx.Geometry(ctx, pts, omega, 1e-10, tx, 0.0 * tx, tc, qbx.options(p=0, direct=True))
+    sig = _dev(np.ones((1, 1), dtype=np.complex128))
+    u = geo.eval(sig if which == "S" else None, sig if which == "D" else None).cpu().numpy()[0]
+    n = 0 if which == "S" else 1
+
+    def hankel(x):
+        x = mp.mpf(x)
+        if x < 1e10:
+            return mp.besselj(n, x) + 1j * mp.bessely(n, x)
+        # Hankel's expansion, the next term below 1e-20
+        return mp.sqrt(2 / (mp.pi * x)) * mp.expj(x - n * mp.pi / 2 - mp.pi / 4) * (1 + 1j * (4 * n * n - 1) / (8 * x))
+    with mp.workdps(140):
+        ref = np.array([complex(0.25j * (mp.mpf(omega) * np.sign(v) if n else 1) * hankel(omega * abs(v))) for v in tx])
+    err = np.abs(u - ref) / np.abs(ref)
+    print(f"omega 2^{k} {which} bound {bound}: {err.max():.2e}", flush=True)
+    assert (err <= 4e-15).all()
+
+
+# Arguments whose square underflows.
+@pytest.mark.parametrize("bound", [True, False])
+@pytest.mark.parametrize("which", ["S", "D"])
+@pytest.mark.parametrize("k", [-600, -520])
+def test_hankel_at_tiny_arguments(ctx, which, bound, k):
+    _hankel_at(ctx, which, bound, k)
