@@ -228,8 +228,9 @@ __device__ __forceinline__ double log_two_over_pi(double z)
     return fma(de, 0.4412712003053032, fma(de, -1.4923443078826812e-17, 1.27323954473516268615 * lm));
 }
 
-// sin x and cos x, 0 <= x <= 1e14: reduction by multiples k of pi/2 in two
+// sin x and cos x, 0 <= x <= kPhaseMax: reduction by multiples k of pi/2 in two
 // parts, of which the first is exact and the second off by k 1e-33.
+constexpr double kPhaseMax = 1e14;
 __device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
 {
     double k = rint(x * 0.63661977236758134308);
@@ -250,6 +251,18 @@ __device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
     c = ((q + 1) & 2) ? -v : v;
 }
 
+// sin x, cos x and 1/sqrt(pi x) beyond kPhaseMax: the device library's
+// reduction.  A call, and made only where distances are free (FAR: near field,
+// direct sums, smooth rule), so that registers stay as they are: inlined, it
+// took 34 more VGPRs of the near field (a wave a SIMD less at p <= 8).  Bases of
+// boxes need no such arguments: their order is at most 1024.
+__device__ __attribute__((noinline)) void far_phase(double x, double &s, double &c, double &f)
+{
+    f = 0.56418958354775628695 / sqrt(x);
+    if (x < __builtin_huge_val()) sincos(x, &s, &c);
+    else s = c = 0.0;                        // H_n vanishes at infinity
+}
+
 // H_0(x) and H_1(x), x > 0, with ix = 1/x, in two ranges: up to 4 polynomials
 // in x^2 beside the logarithm (about 90 double-precision instructions), above
 // it modulus-and-phase form with polynomials in 1/x^2 (about 130); see
@@ -263,6 +276,7 @@ __device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
 // the 1e-16 of the upper form).
 constexpr double kHankelSmallX = 4.0;
 
+template <bool FAR>
 __device__ __forceinline__ void hankel01(double x, double ix, cd &h0, cd &h1)
 {
     const double two_over_pi = 0.63661977236758134308;
@@ -278,25 +292,26 @@ __device__ __forceinline__ void hankel01(double x, double ix, cd &h0, cd &h1)
         return;
     }
     poly4<kHankelLargeRows>(kHankelLarge, fma(ix * ix, 32.0, -1.0), p);
-    double sn, cs;
-    fast_sincos(x, sn, cs);
     // e = sqrt(2/(pi x)) e^{i (x - pi/4)}; H_1 has a further -i
-    double f = fast_rsqrt(3.14159265358979323846 * x);
-    if (x > 1e14) f = 0.0, sn = cs = 0.0;     // x has no phase left (plans end far below)
+    double sn, cs, f;
+    if (!FAR || x <= kPhaseMax) {
+        fast_sincos(x, sn, cs);
+        f = fast_rsqrt(3.14159265358979323846 * x);
+    } else {
+        far_phase(x, sn, cs, f);
+    }
     cd e = mk(f * (cs + sn), f * (sn - cs));
     double q0 = p[1] * ix, q1 = p[3] * ix;
     h0 = mk(fma(p[0], e.x, fma(-q0, e.y, e.x)), fma(p[0], e.y, fma(q0, e.x, e.y)));
     h1 = mk(fma(p[2], e.y, fma(q1, e.x, e.y)), -fma(p[2], e.x, fma(-q1, e.y, e.x)));
 }
 
-__device__ __forceinline__ void hankel01(double x, cd &h0, cd &h1) { hankel01(x, 1.0 / x, h0, h1); }
-
 // A_n = tau^n H_n(x), n = 0..N, written to out[n * stride].  With
 // tau = min(1, x/2) the sequence stays below (n-1)! in magnitude.
 __device__ inline void scaled_hankel_seq(double x, double tau, int N, cd *out, long long stride)
 {
     cd h0, h1;
-    hankel01(x, h0, h1);
+    hankel01<false>(x, 1.0 / x, h0, h1);
     cd a0 = h0, a1 = tau * h1;
     out[0] = a0;
     if (N >= 1) out[stride] = a1;

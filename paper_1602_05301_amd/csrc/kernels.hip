@@ -1184,7 +1184,7 @@ __device__ __forceinline__ void p2qbxl_pair(double omega, double iomega, double 
     double x = omega * r, ix = refine_inverse(x, iomega * ir);
     cd u = mk(dx * ir, dy * ir);
     cd H0, H1;
-    hankel01(x, ix, H0, H1);
+    hankel01<true>(x, ix, H0, H1);
     cd c = (0.5 * omega) * qD;
     cd v = mk(nx, ny) * conj(u);
     double vr2 = 2.0 * v.x, vi2 = 2.0 * v.y;
@@ -1928,7 +1928,7 @@ __device__ __forceinline__ void smooth_body(const DevGeom &g, int nd, const cd *
             double r, ir;
             dist_and_inverse(dx * dx + dy * dy, r, ir);
             cd h0, h1;
-            hankel01(g.omega * r, iomega * ir, h0, h1);
+            hankel01<true>(g.omega * r, iomega * ir, h0, h1);
             cd dh = (g.omega * (dx * g.snx[j] + dy * g.sny[j]) * ir) * h1;
 #pragma unroll
             for (int e = 0; e < SMOOTH_ND; ++e)

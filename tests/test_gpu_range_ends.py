@@ -57,3 +57,12 @@ def _hankel_at(ctx, which, bound, k):
 @pytest.mark.parametrize("k", [-600, -520])
 def test_hankel_at_tiny_arguments(ctx, which, bound, k):
     _hankel_at(ctx, which, bound, k)
+
+
+# Arguments on both sides of 1e14, where the phase takes another reduction, and
+# far beyond.
+@pytest.mark.parametrize("bound", [True, False])
+@pytest.mark.parametrize("which", ["S", "D"])
+@pytest.mark.parametrize("k", [45, 47, 52, 60, 300])
+def test_hankel_at_huge_arguments(ctx, which, bound, k):
+    _hankel_at(ctx, which, bound, k)
