@@ -1399,7 +1399,7 @@ __global__ void __launch_bounds__(64) k_p2qbxl_direct(DevGeom g, int nd, int G, 
 // centre; the v values enter a sliding register window, so each step costs
 // one Hs load and one ahat load for 8 complex multiply-adds.
 // ---------------------------------------------------------------------------
-constexpr size_t LDS_BUDGET = 64 * 1024;
+constexpr size_t LDS_BUDGET = 64 * 1024, LDS_PER_CU = 160 * 1024;
 constexpr int QCG_MAX = 16;   // centres per group (upper bound)
 
 size_t m2qbxl_lds_bytes(int nd, int Pw, int p, int cg)
@@ -1667,25 +1667,50 @@ __global__ void k_wsum(DevGeom g, int nd, const int *leaf_list, const int *leaf_
 // 321 for 200000 nodes (p = 9); now 54, 172 and 253.
 // ---------------------------------------------------------------------------
 constexpr int L2Q_THREADS = 256;   // lanes per item: 16 slots x 4 l-blocks x 4 quarters
-constexpr int L2Q_PAD = 16;        // zeros around a run's locals and a centre's J_n
+constexpr int L2Q_PAD = 16;        // zeros around a run's locals (and around a wide J_n row)
 
-// Entries of a centre's J_n row in LDS (n = -N..N and zeros around, N = rows - 1).
-__host__ __device__ constexpr int l2q_jrow(int rows) { return 2 * (rows - 1) + 1 + 2 * L2Q_PAD; }
+// Entries of a centre's J_n row in LDS, N = rows - 1, the row lengths odd (banks):
+// wide, n = -N..N and zeros around; else n = 0..N and zeros for a step past them.
+__host__ __device__ constexpr int l2q_jrow(int rows, bool wide)
+{
+    return wide ? 2 * (rows - 1) + 1 + 2 * L2Q_PAD : (rows + QBLK) | 1;
+}
 
-size_t l2qbxl_lds_bytes(int P, int cap, int rows)
+size_t l2qbxl_lds_bytes(int P, int cap, int rows, bool wide)
 {
     // one density's locals of every run, the centres' directions, their J_n rows
-    return sizeof(cd) * ((size_t)L2Q_SEGS * (2 * P + 1 + 2 * L2Q_PAD) + (size_t)cap) +
-           sizeof(double) * (size_t)cap * l2q_jrow(rows);
+    return sizeof(cd) * ((size_t)std::min(L2Q_SEGS, cap) * (2 * P + 1 + 2 * L2Q_PAD) + (size_t)cap) +
+           sizeof(double) * (size_t)cap * l2q_jrow(rows, wide);
 }
+
+// Two items a CU: at p = 14, 16 centres an item up to order 295, 8 up to 405.
+constexpr size_t L2Q_LDS_MAX = LDS_PER_CU / 2;
 
 int l2qbxl_item_cap(int Pmax, int rows)
 {
     int cap = L2Q_CAP_MAX;
-    while (cap > 1 && l2qbxl_lds_bytes(Pmax, cap, rows) > LDS_BUDGET) cap >>= 1;
+    while (cap > 1 && l2qbxl_lds_bytes(Pmax, cap, rows, false) > L2Q_LDS_MAX) cap >>= 1;
     return cap;
 }
 
+// Wide rows save the sign and the direction of each step but are twice as long:
+// taken while four items still share a CU, which is what their registers allow
+// (order 75 at p = 14).  32768 nodes, p = 14, one and four densities, wide and
+// not: order 54 51 and 157 us, 52 and 153; 67 57 and 168, 60 and 174; 80 72 and
+// 203, 64 and 182; 110 99 and 270, 69 and 194; 139 108 and 283, 81 and 223.
+static bool l2qbxl_wide(int Pmax, int cap, int rows)
+{
+    return cap == L2Q_CAP_MAX && 4 * l2qbxl_lds_bytes(Pmax, cap, rows, true) <= LDS_PER_CU;
+}
+
+// Orders taken: four runs' locals and a centre's J_n within the budget (480 at
+// p = 14); leaves of higher orders are refused at the evaluation.
+static bool l2qbxl_fits(int Pmax, int rows)
+{
+    return sizeof(cd) * ((size_t)L2Q_SEGS * (2 * Pmax + 1) + 1) + sizeof(double) * (size_t)rows <= LDS_BUDGET;
+}
+
+template <bool WIDE>
 __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int *items, const double *crad,
                                             const cd *loc, cd *coef, int cap, int rows, BlockId bid)
 {
@@ -1712,7 +1737,7 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
     int p = g.p, nq = 2 * p + 1;
     int nblk = (nq + QBLK - 1) / QBLK;
     int tid = threadIdx.x;
-    const int JR = l2q_jrow(rows), J0 = rows - 1 + L2Q_PAD;   // row length, place of n = 0
+    const int JR = l2q_jrow(rows, WIDE), J0 = WIDE ? rows - 1 + L2Q_PAD : 0;   // row length, place of n = 0
     cd *Gb = reinterpret_cast<cd *>(lds_raw);          // [gsum]: run r's local at go[r]
     cd *U = Gb + gsum;                                 // [cap]
     double *Jt = reinterpret_cast<double *>(U + cap);  // [cap][JR]
@@ -1728,17 +1753,17 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
         double rr = sqrt(dx * dx + dy * dy);
         U[t] = rr > 0.0 ? mk(dx / rr, dy / rr) : mk(1.0, 0.0);
     }
-    // J_n for both signs of n (J_{-n} = (-1)^n J_n), zero past the run's
-    // orders; 16 lanes read a centre's row
+    // J_n, zero past the run's orders (wide: for both signs of n, J_{-n} =
+    // (-1)^n J_n); 16 lanes read a centre's row
     for (int t = tid >> 4; t < T; t += L2Q_THREADS / 16) {
         int r = run_of(t);
         const double *row = crad + (long long)(rc0[r] + t - so[r]) * rows;
         double *J = Jt + t * JR + J0;
 #pragma unroll 4
-        for (int n = tid & 15; n < rows + L2Q_PAD; n += 16) {
+        for (int n = tid & 15; n < JR - J0; n += 16) {
             double v = n < rows ? row[n] : 0.0;
             J[n] = v;
-            J[-n] = (n & 1) ? -v : v;
+            if (WIDE) J[-n] = (n & 1) ? -v : v;
         }
     }
     for (int d = 0; d < nd; ++d) {
@@ -1768,14 +1793,17 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
             int ci = rc0[r] + t - so[r];
             if (active) {
                 // this lane's quarter [na, nb) of the block's n range, in whole
-                // steps of QBLK: what a step adds past the range's end is
-                // zero (no such local, or no such J_n) or a term as good
+                // steps of QBLK: what a step adds past the range's ends is
+                // zero (no such local, or no such J_n) or a term as good.
+                // Without the wide rows steps start at multiples of QBLK, so
+                // that none has both signs of n, and those below zero read J_n
+                // backward.
                 const auto rng = g.l2q_rng + rl[r] * nblk + blk;
-                int n_lo = rng->x, n_end = rng->y + 1;
+                int n_lo = WIDE ? rng->x : rng->x & -QBLK, n_end = rng->y + 1;
                 int cs = (n_end - n_lo + QSPLIT * QBLK - 1) / (QSPLIT * QBLK) * QBLK;
                 int na = n_lo + sp * cs, nb = min(na + cs, n_end);
                 const cd *G = Gb + go[r] + L2Q_PAD + rP[r] + l0 - na;    // G[-s]: local of order l0 - (na + s)
-                const double *J = Jt + t * JR + J0 + na;
+                const double *J = Jt + t * JR + J0 + (WIDE ? na : 0);
                 if (na < nb) {
                     cd ph = unit_ipow(conj(u), l0 - na + QBLK);          // conj(u)^k, k = l0 - n
 #pragma unroll
@@ -1785,11 +1813,15 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
                     }
 #pragma unroll 1
                     for (int n0 = na; n0 < nb; n0 += QBLK) {
+                        const bool below = !WIDE && n0 < 0;
+                        const double *Jn = WIDE ? J : J + (below ? -n0 : n0);
+                        const int dn = below ? -1 : 1;
 #pragma unroll
                         for (int s = 0; s < QBLK; ++s) {
                             win[s] = G[-s] * ph;
                             ph = ph * u;
-                            double jn = J[s];
+                            double jn = Jn[s * dn];
+                            if (s & 1) jn = below ? -jn : jn;
 #pragma unroll
                             for (int e = 0; e < QBLK; ++e) {
                                 cd w = win[(s - e + QBLK) % QBLK];
@@ -1798,7 +1830,7 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
                             }
                         }
                         G -= QBLK;
-                        J += QBLK;
+                        if (WIDE) J += QBLK;
                     }
                 }
             }
@@ -1828,9 +1860,10 @@ __device__ __forceinline__ void l2qbxl_body(const DevGeom &g, int nd, const int 
     }
 }
 
+template <bool WIDE>
 __global__ void __launch_bounds__(L2Q_THREADS) k_l2qbxl(DevGeom g, int nd, const int *items, const double *crad, const cd *loc, cd *coef, int cap, int rows)
 {
-    l2qbxl_body(g, nd, items, crad, loc, coef, cap, rows, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
+    l2qbxl_body<WIDE>(g, nd, items, crad, loc, coef, cap, rows, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
 // ---------------------------------------------------------------------------
@@ -2120,10 +2153,11 @@ __global__ void kf_wsum(const FRec *recs, const int *map)
               CP(cd *, out0), bid);
 }
 
+template <bool WIDE>
 __global__ void __launch_bounds__(L2Q_THREADS) kf_l2qbxl(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
-    l2qbxl_body(g, r.nd, CP(const int *, in0), CP(const double *, in1), CP(const cd *, in2), CP(cd *, out0), r.i0,
+    l2qbxl_body<WIDE>(g, r.nd, CP(const int *, in0), CP(const double *, in1), CP(const cd *, in2), CP(cd *, out0), r.i0,
                 (int)r.n64, bid);
 }
 
@@ -2404,9 +2438,11 @@ hipError_t launch_l2qbxl(const DevGeom &g, int nd, const int *items, int n, int 
 {
     if (!n) return hipSuccess;
     if (Pmax + g.p + QBLK > crad_rows || cap < 1 || cap > L2Q_CAP_MAX) return hipErrorInvalidValue;
-    size_t lds = l2qbxl_lds_bytes(Pmax, cap, crad_rows);
-    if (lds > LDS_BUDGET) return hipErrorInvalidValue;
-    k_l2qbxl<<<n, L2Q_THREADS, lds, s>>>(g, nd, items, crad, loc, coef, cap, crad_rows);
+    const bool wide = l2qbxl_wide(Pmax, cap, crad_rows);
+    size_t lds = l2qbxl_lds_bytes(Pmax, cap, crad_rows, wide);
+    if (!l2qbxl_fits(Pmax, crad_rows) || lds > L2Q_LDS_MAX) return hipErrorInvalidValue;
+    if (wide) k_l2qbxl<true><<<n, L2Q_THREADS, lds, s>>>(g, nd, items, crad, loc, coef, cap, crad_rows);
+    else k_l2qbxl<false><<<n, L2Q_THREADS, lds, s>>>(g, nd, items, crad, loc, coef, cap, crad_rows);
     QBX_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2640,11 +2676,12 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
         // r.i0: the items' centre capacity; aux: the J_n table's rows
         for (const auto &it : items) {
             if (it.P + it.h->p + QBLK > it.aux || it.r.i0 < 1 || it.r.i0 > L2Q_CAP_MAX) return hipErrorInvalidValue;
-            size_t lds = l2qbxl_lds_bytes(it.P, it.r.i0, it.aux);
-            if (lds > LDS_BUDGET) return hipErrorInvalidValue;
+            const bool wide = l2qbxl_wide(it.P, it.r.i0, it.aux);
+            size_t lds = l2qbxl_lds_bytes(it.P, it.r.i0, it.aux, wide);
+            if (!l2qbxl_fits(it.P, it.aux) || lds > L2Q_LDS_MAX) return hipErrorInvalidValue;
             FRec r = it.r;
             r.n64 = it.aux;
-            add(kind, 0, r, it.n, it.n, lds, L2Q_THREADS);
+            add(kind, wide, r, it.n, it.n, lds, L2Q_THREADS);
         }
         break;
     case FK_EVAL:
@@ -2747,7 +2784,10 @@ hipError_t fused_launch(const FLaunch &L, const unsigned char *dev, hipStream_t 
         break;
     case FK_M2QBXL: FL(kf_m2qbxl); break;
     case FK_WSUM: FL(kf_wsum); break;
-    case FK_L2QBXL: FL(kf_l2qbxl); break;
+    case FK_L2QBXL:
+        if (L.variant) FL(kf_l2qbxl<true>);
+        else FL(kf_l2qbxl<false>);
+        break;
     case FK_EVAL: FL(kf_eval); break;
     case FK_SMOOTH: FL(kf_smooth); break;
     default: return hipErrorInvalidValue;
