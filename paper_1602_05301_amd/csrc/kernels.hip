@@ -1899,7 +1899,16 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
     double s = 1.0;
     int top = 0;                                                 // at rho = 0 only l = 0 counts
     J[0] = 1.0;
-    if (x != 0.0) {
+    if (x < 1e-8) {
+        // J_n = (x/2)^n / n! to rounding; the recurrence below would leave the
+        // exponent range within a step or two of the smallest x
+        if (x != 0.0) top = p;
+        double f = 1.0;
+        for (int n = 1; n <= top; ++n) {
+            f *= 0.5 * x / n;
+            J[n * EVAL_THREADS] = f;
+        }
+    } else {
         top = p;
         double inv = 2.0 / x;
         double fp1 = 0.0, f = 1e-280, sum = 0.0;

@@ -101,3 +101,27 @@ def test_l2qbxl_at_high_leaf_orders(ctx, omega, order):
     torch.cuda.synchronize()
     assert torch.equal(one[0], u[1]) and torch.equal(both[1], u)
     assert torch.equal(both[0], low.eval(_dev(ss), _dev(sd)))
+
+
+# Targets so close to their centre, or to it in wavelengths, that the downward
+# recurrence leaves the exponent range in a few steps: what is left of the
+# expansion is its order 0, which the coefficients of the same call give, and
+# orders +-1 times x / 2, which the tolerance covers (coefficients stay below 10
+# here), and rounding.
+@pytest.mark.parametrize("p", [0, 1, 5, 14, 40])
+def test_evaluation_beside_the_centre(ctx, p):
+    from paper_1602_05301_amd import qbx
+    r = np.random.default_rng(p)
+    ang = r.uniform(0, 2 * np.pi, 5)
+    pts = inputs.Points(40 * np.cos(ang), 40 * np.sin(ang), np.ones(5), np.cos(ang), np.sin(ang), np.ones(5),
+                        np.zeros(1), np.zeros(1), np.ones(1))
+    tx = np.concatenate([[0.0], 10.0 ** -np.arange(12.0, 160.0)])
+    geo = qbx.Geometry(ctx, pts, 1.0, 1e-10, tx, 0.0 * tx, np.zeros(tx.size, dtype=np.int32),
+                       qbx.options(p=p, direct=True))
+    sig = _dev(inputs.complex_gaussian(r, (2, 5)))
+    u, coef = (a.cpu().numpy() for a in geo.eval(sig, None, coef=True))
+    a0 = coef.reshape(2, 2 * p + 1)[:, p:p + 1]
+    assert np.abs(coef).max() < 10.0
+    err = np.abs(u - a0)
+    print(f"p {p}: {err.max():.2e}", flush=True)
+    assert (err <= 1e-15 + 10.0 * tx).all()
