@@ -445,10 +445,16 @@ qbx_status upload(qbx_geom_s *G)
     g.cx = ar.upload(ccx); g.cy = ar.upload(ccy); g.ctr_perm = ar.upload(cperm);
 
     std::vector<int> tcs(pl.nt), smooth;
+    g.eval_ends = 0;
     for (int64_t m = 0; m < pl.nt; ++m) {
         int v = pl.tgt_ctr[m];
         tcs[m] = v >= 0 ? rank[v] : -1;
-        if (v < 0) smooth.push_back((int)m);
+        if (v < 0) {
+            smooth.push_back((int)m);
+            continue;
+        }
+        double x = pl.omega * std::hypot(pl.tx[m] - pl.cx[v], pl.ty[m] - pl.cy[v]);
+        if (x > kEvalUpX || (x < kEvalLeadX && x != 0.0)) g.eval_ends = 1;
     }
     g.tx = ar.upload(pl.tx); g.ty = ar.upload(pl.ty); g.tgt_cs = ar.upload(tcs);
     g.smooth_list = ar.upload(smooth);

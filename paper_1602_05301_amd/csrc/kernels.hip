@@ -1876,11 +1876,18 @@ __global__ void __launch_bounds__(L2Q_THREADS) k_l2qbxl(DevGeom g, int nd, const
 // in one loop: 19 us for 512 targets, 15 for 32768 (p = 14), 39 for
 // four densities of them, 25 for 200000 FP64 sources; now 9.6,
 // 10.6, 21.3, 24.6.
+// ENDS: some target is nearer to its centre than kEvalLeadX or farther than
+// kEvalUpX (in 1/omega).  Near, J_n = (x/2)^n / n! to rounding, and the
+// recurrence would leave the exponent range within a step or two at the smallest
+// x; far, J_n comes upward from J_0 and J_1, stable for n < x, as the downward
+// recurrence takes x steps, rounds at each, and its start is an int.  A form of
+// its own, so that the common one makes no call.
 // ---------------------------------------------------------------------------
 constexpr int EVAL_THREADS = 64;   // few targets then still reach every CU
 
 size_t eval_lds_bytes(int p) { return sizeof(double) * EVAL_THREADS * (size_t)(p + 1); }
 
+template <bool ENDS>
 __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd *coef, cd *u, BlockId bid)
 {
     extern __shared__ double lds_raw[];
@@ -1899,16 +1906,26 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
     double s = 1.0;
     int top = 0;                                                 // at rho = 0 only l = 0 counts
     J[0] = 1.0;
-    if (x < 1e-8) {
-        // J_n = (x/2)^n / n! to rounding; the recurrence below would leave the
-        // exponent range within a step or two of the smallest x
-        if (x != 0.0) top = p;
+    if (ENDS && x != 0.0 && x < kEvalLeadX) {
+        top = p;
         double f = 1.0;
-        for (int n = 1; n <= top; ++n) {
+        for (int n = 1; n <= p; ++n) {
             f *= 0.5 * x / n;
             J[n * EVAL_THREADS] = f;
         }
-    } else {
+    } else if (ENDS && x > kEvalUpX) {
+        top = p;
+        cd h0, h1;
+        hankel01<true>(x, 1.0 / x, h0, h1);
+        double a = h0.x, b = h1.x;
+        J[0] = a;
+        for (int n = 1; n <= p; ++n) {
+            J[n * EVAL_THREADS] = b;
+            double c = fma(2.0 * n / x, b, -a);
+            a = b;
+            b = c;
+        }
+    } else if (x != 0.0) {
         top = p;
         double inv = 2.0 / x;
         double fp1 = 0.0, f = 1e-280, sum = 0.0;
@@ -1942,9 +1959,10 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
     }
 }
 
+template <bool ENDS>
 __global__ void __launch_bounds__(EVAL_THREADS) k_qbx_eval(DevGeom g, int nd, const cd *coef, cd *u)
 {
-    qbx_eval_body(g, nd, coef, u, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
+    qbx_eval_body<ENDS>(g, nd, coef, u, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
 // Smooth (unmodified Gauss) rule at unassociated targets, over all sources.
@@ -2170,10 +2188,11 @@ __global__ void __launch_bounds__(L2Q_THREADS) kf_l2qbxl(const FRec *recs, const
                 (int)r.n64, bid);
 }
 
+template <bool ENDS>
 __global__ void __launch_bounds__(EVAL_THREADS) kf_eval(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
-    qbx_eval_body(g, r.nd, CP(const cd *, in0), CP(cd *, out0), bid);
+    qbx_eval_body<ENDS>(g, r.nd, CP(const cd *, in0), CP(cd *, out0), bid);
 }
 
 __global__ void __launch_bounds__(64) kf_smooth(const FRec *recs, const int *map)
@@ -2459,7 +2478,9 @@ hipError_t launch_l2qbxl(const DevGeom &g, int nd, const int *items, int n, int 
 hipError_t launch_qbx_eval(const DevGeom &g, int nd, const cd *coef, cd *u, hipStream_t s)
 {
     if (!g.nt) return hipSuccess;
-    k_qbx_eval<<<(g.nt + EVAL_THREADS - 1) / EVAL_THREADS, EVAL_THREADS, eval_lds_bytes(g.p), s>>>(g, nd, coef, u);
+    const int blocks = (g.nt + EVAL_THREADS - 1) / EVAL_THREADS;
+    if (g.eval_ends) k_qbx_eval<true><<<blocks, EVAL_THREADS, eval_lds_bytes(g.p), s>>>(g, nd, coef, u);
+    else k_qbx_eval<false><<<blocks, EVAL_THREADS, eval_lds_bytes(g.p), s>>>(g, nd, coef, u);
     QBX_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2696,7 +2717,7 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
     case FK_EVAL:
         for (const auto &it : items) {
             long long b = ((long long)it.h->nt + EVAL_THREADS - 1) / EVAL_THREADS;
-            add(kind, 0, it.r, b, b, eval_lds_bytes(it.h->p), EVAL_THREADS);
+            add(kind, it.h->eval_ends, it.r, b, b, eval_lds_bytes(it.h->p), EVAL_THREADS);
         }
         break;
     case FK_SMOOTH:
@@ -2797,7 +2818,10 @@ hipError_t fused_launch(const FLaunch &L, const unsigned char *dev, hipStream_t 
         if (L.variant) FL(kf_l2qbxl<true>);
         else FL(kf_l2qbxl<false>);
         break;
-    case FK_EVAL: FL(kf_eval); break;
+    case FK_EVAL:
+        if (L.variant) FL(kf_eval<true>);
+        else FL(kf_eval<false>);
+        break;
     case FK_SMOOTH: FL(kf_smooth); break;
     default: return hipErrorInvalidValue;
     }

@@ -32,10 +32,16 @@ struct RowBlk {
     int nth;        // of the i-th row block of a table: the row block with the i-th most blocks
 };
 
+// x = omega |t - c| below which the evaluation takes J_n by its leading term
+// (the next is x^2 / 4 of it) and above which by the upward recurrence (stable
+// for n < x; orders are at most 40).
+constexpr double kEvalLeadX = 1e-8, kEvalUpX = 100.0;
+
 // All pointers are device pointers.  Points are in tree (Morton) order.
 struct DevGeom {
     int ns, nc, nt, nb, nlev, p, n_smooth;
     int max_leaf_ctr;                          // most centres in one leaf
+    int eval_ends;                             // a bound target with omega |t - c| beyond one of these bounds
     double omega;
     const QBX_G double *sx, *sy, *sw, *snx, *sny;   // sorted sources
     const QBX_G int *src_perm;                       // sorted -> user source index

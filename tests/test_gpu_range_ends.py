@@ -125,3 +125,48 @@ def test_evaluation_beside_the_centre(ctx, p):
     err = np.abs(u - a0)
     print(f"p {p}: {err.max():.2e}", flush=True)
     assert (err <= 1e-15 + 10.0 * tx).all()
+
+
+# Targets far from their centre, on both sides of the bound of the upward
+# recurrence and past the range of an int, against mpmath from the coefficients
+# of the same call; alone and batched.  The tolerance is of the sum of moduli,
+# |J_n| about sqrt(2 / (pi x)) there (up to 3 times that at n = 40 and x = 99):
+# 2e-14 as for nearer targets, and x 1.1e-16 where the recurrence takes x steps.
+@pytest.mark.parametrize("p", [0, 1, 14, 40])
+def test_evaluation_far_from_the_centre(ctx, p):
+    mp = pytest.importorskip("mpmath")
+    from paper_1602_05301_amd import qbx
+    r = np.random.default_rng(p)
+    x = np.array([60.0, 99.0, 101.0, 9999.0, 123456.0, 2.0 ** 31, 5.0 * 2.0 ** 30, 3.0 * 2.0 ** 45, 2.0 ** 60])
+    pts = inputs.Points(np.array([40.0]), np.zeros(1), np.ones(1), np.ones(1), np.zeros(1), np.ones(1),
+                        np.zeros(1), np.zeros(1), np.ones(1))
+    geo = qbx.Geometry(ctx, pts, 1.0, 1e-10, x, 0.0 * x, np.zeros(x.size, dtype=np.int32),
+                       qbx.options(p=p, direct=True))
+    sig = _dev(inputs.complex_gaussian(r, (1, 1)))
+    u, coef = (a.cpu().numpy() for a in geo.eval(sig, None, coef=True))
+    a = coef.reshape(2 * p + 1)
+    with mp.workdps(60):
+        J = []
+        for v in x:
+            if v < 1e9:
+                col = [mp.besselj(n, mp.mpf(v)) for n in range(p + 1)]
+            else:                                    # two terms of the expansion, the next below 1e-20
+                col = []
+                for n in range(2):
+                    w = mp.mpf(v) - n * mp.pi / 2 - mp.pi / 4
+                    m = 4 * n * n
+                    col.append(mp.sqrt(2 / (mp.pi * v)) * (mp.cos(w) - mp.sin(w) * (m - 1) / (8 * mp.mpf(v))))
+                while len(col) <= p:
+                    n = len(col) - 1
+                    col.append(2 * n / mp.mpf(v) * col[n] - col[n - 1])
+            J.append([float(c) for c in col[:p + 1]])
+    J = np.array(J).T
+    l = np.arange(-p, p + 1)
+    Jl = J[abs(l)] * np.where((l < 0) & (l % 2 == 1), -1.0, 1.0)[:, None]
+    err = np.abs(u[0] - (a[:, None] * Jl).sum(0)) / (np.abs(a).sum() * np.sqrt(2 / (np.pi * x)))
+    print(f"p {p}: {err}", flush=True)
+    assert (err <= 2e-14 + np.where(x < 100.0, 3.3e-16 * x, 0.0)).all()
+    both = torch.empty((1, x.size), dtype=torch.complex128, device="cuda:0")
+    ctx.eval_batch([geo], [sig], [None], [both])
+    torch.cuda.synchronize()
+    assert np.array_equal(both.cpu().numpy(), u)
