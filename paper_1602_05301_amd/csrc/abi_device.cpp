@@ -456,6 +456,15 @@ qbx_status upload(qbx_geom_s *G)
         double x = pl.omega * std::hypot(pl.tx[m] - pl.cx[v], pl.ty[m] - pl.cy[v]);
         if (x > kEvalUpX || (x < kEvalLeadX && x != 0.0)) g.eval_ends = 1;
     }
+    // distances are at most the diameter of the origin-centred disk of all points
+    double rmax_all = 0.0;
+    auto reach = [&](const std::vector<double> &x, const std::vector<double> &y) {
+        for (size_t i = 0; i < x.size(); ++i) rmax_all = std::max(rmax_all, std::hypot(x[i], y[i]));
+    };
+    reach(pl.sx, pl.sy);
+    reach(pl.cx, pl.cy);
+    reach(pl.tx, pl.ty);
+    g.far = 2.0 * pl.omega * rmax_all > kPhaseMax;
     g.tx = ar.upload(pl.tx); g.ty = ar.upload(pl.ty); g.tgt_cs = ar.upload(tcs);
     g.smooth_list = ar.upload(smooth);
     // in FMM mode the order-0 sub-geometry serves these targets

@@ -254,10 +254,10 @@ __device__ __forceinline__ void fast_sincos(double x, double &s, double &c)
 }
 
 // sin x, cos x and 1/sqrt(pi x) beyond kPhaseMax: the device library's
-// reduction.  A call, and made only where distances are free (FAR: near field,
-// direct sums, smooth rule), so that registers stay as they are: inlined, it
-// took 34 more VGPRs of the near field (a wave a SIMD less at p <= 8).  Bases of
-// boxes need no such arguments: their order is at most 1024.
+// reduction, for geometries with such distances only (FAR: their near field,
+// direct sums and smooth rule have kernels of their own, as a call or 34 more
+// VGPRs slow the common ones).  Bases of boxes need no such arguments: their
+// order is at most 1024.
 __device__ __attribute__((noinline)) void far_phase(double x, double &s, double &c, double &f)
 {
     f = 0.56418958354775628695 / sqrt(x);

@@ -1174,7 +1174,7 @@ __global__ void __launch_bounds__(64) k_p2l_xc(DevGeom g, const int *list, const
 // barriers and the second half's start cost more than the waves hide).
 // ---------------------------------------------------------------------------
 // Sums of a lane: E_m at acc[2m - 1], F_m at acc[2m], E_0 at acc[0].
-template <int PB>
+template <int PB, bool FAR>
 __device__ __forceinline__ void p2qbxl_pair(double omega, double iomega, double cx, double cy, double sx,
                                             double sy, double nx, double ny, cd qS, cd qD, cd *acc)
 {
@@ -1184,7 +1184,7 @@ __device__ __forceinline__ void p2qbxl_pair(double omega, double iomega, double 
     double x = omega * r, ix = refine_inverse(x, iomega * ir);
     cd u = mk(dx * ir, dy * ir);
     cd H0, H1;
-    hankel01<true>(x, ix, H0, H1);
+    hankel01<FAR>(x, ix, H0, H1);
     cd c = (0.5 * omega) * qD;
     cd v = mk(nx, ny) * conj(u);
     double vr2 = 2.0 * v.x, vi2 = 2.0 * v.y;
@@ -1277,7 +1277,7 @@ size_t p2qbxl_lds_bytes()
     return sizeof(cd) * ((size_t)P2Q_RED * P2Q_THREADS + 2 * P2Q_SCH) + sizeof(double) * 4 * P2Q_SCH;
 }
 
-template <int PB>
+template <int PB, bool FAR>
 __device__ __forceinline__ void p2qbxl_body(const DevGeom &g, int nd, const int *items, const cd *qs, const cd *qd, cd *coef, BlockId bid)
 {
     extern __shared__ double lds_raw[];
@@ -1320,7 +1320,7 @@ __device__ __forceinline__ void p2qbxl_body(const DevGeom &g, int nd, const int 
                 if (active) {
 #pragma unroll 1
                     for (int f = part; f < cnt; f += parts)
-                        p2qbxl_pair<PB>(g.omega, iomega, cx, cy, SX[f], SY[f], NX[f], NY[f], QS[f], QD[f], acc);
+                        p2qbxl_pair<PB, FAR>(g.omega, iomega, cx, cy, SX[f], SY[f], NX[f], NY[f], QS[f], QD[f], acc);
                 }
             }
             p2qbxl_alpha<PB>(acc);
@@ -1346,14 +1346,14 @@ __device__ __forceinline__ void p2qbxl_body(const DevGeom &g, int nd, const int 
     }
 }
 
-template <int PB>
+template <int PB, bool FAR>
 __global__ void __launch_bounds__(P2Q_THREADS) k_p2qbxl(DevGeom g, int nd, const int *items, const cd *qs, const cd *qd, cd *coef)
 {
-    p2qbxl_body<PB>(g, nd, items, qs, qd, coef, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
+    p2qbxl_body<PB, FAR>(g, nd, items, qs, qd, coef, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
 // Direct mode: all sources to every centre (Sec. 3.2, oversampled coefficient sum).
-template <int PB>
+template <int PB, bool FAR>
 __device__ __forceinline__ void p2qbxl_direct_body(const DevGeom &g, int nd, int G, const cd *qs, const cd *qd, cd *coef, BlockId bid)
 {
     int parts = 64 / G;
@@ -1371,7 +1371,7 @@ __device__ __forceinline__ void p2qbxl_direct_body(const DevGeom &g, int nd, int
         if (active)
 #pragma unroll 1
             for (int j = part; j < g.ns; j += parts)
-                p2qbxl_pair<PB>(g.omega, iomega, cx, cy, g.sx[j], g.sy[j], g.snx[j], g.sny[j],
+                p2qbxl_pair<PB, FAR>(g.omega, iomega, cx, cy, g.sx[j], g.sy[j], g.snx[j], g.sny[j],
                                 qs[(long long)d * g.ns + j], qd[(long long)d * g.ns + j], acc);
         p2qbxl_alpha<PB>(acc);
         p2qbxl_finish<PB>(acc, G, p, active && part == 0,
@@ -1379,10 +1379,10 @@ __device__ __forceinline__ void p2qbxl_direct_body(const DevGeom &g, int nd, int
     }
 }
 
-template <int PB>
+template <int PB, bool FAR>
 __global__ void __launch_bounds__(64) k_p2qbxl_direct(DevGeom g, int nd, int G, const cd *qs, const cd *qd, cd *coef)
 {
-    p2qbxl_direct_body<PB>(g, nd, G, qs, qd, coef, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
+    p2qbxl_direct_body<PB, FAR>(g, nd, G, qs, qd, coef, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
 // ---------------------------------------------------------------------------
@@ -1971,6 +1971,7 @@ __global__ void __launch_bounds__(EVAL_THREADS) k_qbx_eval(DevGeom g, int nd, co
 // wave sums its lanes by a fixed butterfly.
 constexpr int SMOOTH_ND = 4;                  // densities per pass (the pipeline's chunk)
 
+template <bool FAR>
 __device__ __forceinline__ void smooth_body(const DevGeom &g, int nd, const cd *qs, const cd *qd, cd *u, BlockId bid)
 {
     int idx = bid.x;
@@ -1988,7 +1989,7 @@ __device__ __forceinline__ void smooth_body(const DevGeom &g, int nd, const cd *
             double r, ir;
             dist_and_inverse(dx * dx + dy * dy, r, ir);
             cd h0, h1;
-            hankel01<true>(g.omega * r, iomega * ir, h0, h1);
+            hankel01<FAR>(g.omega * r, iomega * ir, h0, h1);
             cd dh = (g.omega * (dx * g.snx[j] + dy * g.sny[j]) * ir) * h1;
 #pragma unroll
             for (int e = 0; e < SMOOTH_ND; ++e)
@@ -2009,9 +2010,10 @@ __device__ __forceinline__ void smooth_body(const DevGeom &g, int nd, const cd *
     }
 }
 
+template <bool FAR>
 __global__ void __launch_bounds__(64) k_smooth(DevGeom g, int nd, const cd *qs, const cd *qd, cd *u)
 {
-    smooth_body(g, nd, qs, qd, u, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
+    smooth_body<FAR>(g, nd, qs, qd, u, BlockId{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x});
 }
 
 // coef_user[d][l][user(i)] = coef[d][l][i]
@@ -2152,18 +2154,18 @@ __global__ void __launch_bounds__(64) kf_p2l_xc(const FRec *recs, const int *map
     p2l_xc_body<ND>(g, CP(const int *, in0), CP(const cd *, in1), CP(const cd *, in2), CP(cd *, out0), bid);
 }
 
-template <int PB>
+template <int PB, bool FAR>
 __global__ void __launch_bounds__(P2Q_THREADS) kf_p2qbxl(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
-    p2qbxl_body<PB>(g, r.nd, CP(const int *, in0), CP(const cd *, in1), CP(const cd *, in2), CP(cd *, out0), bid);
+    p2qbxl_body<PB, FAR>(g, r.nd, CP(const int *, in0), CP(const cd *, in1), CP(const cd *, in2), CP(cd *, out0), bid);
 }
 
-template <int PB>
+template <int PB, bool FAR>
 __global__ void __launch_bounds__(64) kf_p2qbxl_direct(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
-    p2qbxl_direct_body<PB>(g, r.nd, r.i0, CP(const cd *, in0), CP(const cd *, in1), CP(cd *, out0), bid);
+    p2qbxl_direct_body<PB, FAR>(g, r.nd, r.i0, CP(const cd *, in0), CP(const cd *, in1), CP(cd *, out0), bid);
 }
 
 __global__ void __launch_bounds__(256) kf_m2qbxl(const FRec *recs, const int *map)
@@ -2195,10 +2197,11 @@ __global__ void __launch_bounds__(EVAL_THREADS) kf_eval(const FRec *recs, const 
     qbx_eval_body<ENDS>(g, r.nd, CP(const cd *, in0), CP(cd *, out0), bid);
 }
 
+template <bool FAR>
 __global__ void __launch_bounds__(64) kf_smooth(const FRec *recs, const int *map)
 {
     FUSED_BEGIN
-    smooth_body(g, r.nd, CP(const cd *, in0), CP(const cd *, in1), CP(cd *, out0), bid);
+    smooth_body<FAR>(g, r.nd, CP(const cd *, in0), CP(const cd *, in1), CP(cd *, out0), bid);
 }
 
 #undef CP
@@ -2378,11 +2381,11 @@ hipError_t launch_p2l_x(const DevGeom &g, int nd, const int *list, int n, int Pm
 // workgroups per CU, 358 with eight waves of the X lists as well, 353 with one
 // per item.
 
-template <int PB>
+template <int PB, bool FAR = false>
 static hipError_t p2qbxl_dispatch(const DevGeom &g, int nd, const int *items, int n, const cd *qs,
                                   const cd *qd, cd *coef, hipStream_t s)
 {
-    k_p2qbxl<PB><<<n, P2Q_THREADS, p2qbxl_lds_bytes(), s>>>(g, nd, items, qs, qd, coef);
+    k_p2qbxl<PB, FAR><<<n, P2Q_THREADS, p2qbxl_lds_bytes(), s>>>(g, nd, items, qs, qd, coef);
     return hipGetLastError();
 }
 
@@ -2390,6 +2393,7 @@ hipError_t launch_p2qbxl(const DevGeom &g, int nd, const int *items, int n, cons
                          const cd *qd, cd *coef, hipStream_t s)
 {
     if (!n) return hipSuccess;
+    if (g.far) return p2qbxl_dispatch<40, true>(g, nd, items, n, qs, qd, coef, s);
     if (g.p <= 8) return p2qbxl_dispatch<8>(g, nd, items, n, qs, qd, coef, s);
     if (g.p <= 12) return p2qbxl_dispatch<12>(g, nd, items, n, qs, qd, coef, s);
     if (g.p <= 14) return p2qbxl_dispatch<14>(g, nd, items, n, qs, qd, coef, s);
@@ -2404,13 +2408,13 @@ hipError_t launch_p2qbxl(const DevGeom &g, int nd, const int *items, int n, cons
 // centre), four for large sets.
 static int direct_centres_per_wave(long long nc) { return nc >= 16384 ? 4 : (nc >= 4096 ? 2 : 1); }
 
-template <int PB>
+template <int PB, bool FAR = false>
 static hipError_t p2qbxl_direct_dispatch(const DevGeom &g, int nd, const cd *qs, const cd *qd,
                                          cd *coef, hipStream_t s)
 {
     int G = direct_centres_per_wave(g.nc);
     int blocks = (g.nc + G - 1) / G;
-    k_p2qbxl_direct<PB><<<blocks, 64, 0, s>>>(g, nd, G, qs, qd, coef);
+    k_p2qbxl_direct<PB, FAR><<<blocks, 64, 0, s>>>(g, nd, G, qs, qd, coef);
     return hipGetLastError();
 }
 
@@ -2418,6 +2422,7 @@ hipError_t launch_p2qbxl_direct(const DevGeom &g, int nd, const cd *qs, const cd
                                 hipStream_t s)
 {
     if (!g.nc) return hipSuccess;
+    if (g.far) return p2qbxl_direct_dispatch<40, true>(g, nd, qs, qd, coef, s);
     if (g.p <= 8) return p2qbxl_direct_dispatch<8>(g, nd, qs, qd, coef, s);
     if (g.p <= 12) return p2qbxl_direct_dispatch<12>(g, nd, qs, qd, coef, s);
     if (g.p <= 14) return p2qbxl_direct_dispatch<14>(g, nd, qs, qd, coef, s);
@@ -2488,7 +2493,8 @@ hipError_t launch_qbx_eval(const DevGeom &g, int nd, const cd *coef, cd *u, hipS
 hipError_t launch_smooth(const DevGeom &g, int nd, const cd *qs, const cd *qd, cd *u, hipStream_t s)
 {
     if (!g.n_smooth) return hipSuccess;
-    k_smooth<<<g.n_smooth, 64, 0, s>>>(g, nd, qs, qd, u);
+    if (g.far) k_smooth<true><<<g.n_smooth, 64, 0, s>>>(g, nd, qs, qd, u);
+    else k_smooth<false><<<g.n_smooth, 64, 0, s>>>(g, nd, qs, qd, u);
     QBX_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2528,9 +2534,12 @@ hipError_t launch_coef_out(const DevGeom &g, int nd, const cd *coef, cd *out, hi
 // ---------------------------------------------------------------------------
 namespace {
 
-int p2q_bucket(int p)
+constexpr int kFarBucket = 41;
+
+int p2q_bucket(const DevGeom &g)
 {
-    return p <= 8 ? 8 : p <= 12 ? 12 : p <= 14 ? 14 : p <= 16 ? 16 : p <= 24 ? 24 : p <= 32 ? 32 : 40;
+    const int p = g.p;
+    return g.far ? kFarBucket : p <= 8 ? 8 : p <= 12 ? 12 : p <= 14 ? 14 : p <= 16 ? 16 : p <= 24 ? 24 : p <= 32 ? 32 : 40;
 }
 
 // Appends one launch: records (first block filled in) and the block map.
@@ -2675,7 +2684,7 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
         break;
     case FK_P2QBXL:
         for (const auto &it : items) {
-            int pb = p2q_bucket(it.h->p);
+            int pb = p2q_bucket(*it.h);
             add(kind, pb, it.r, it.n, it.n, p2qbxl_lds_bytes(), P2Q_THREADS);
         }
         break;
@@ -2684,7 +2693,7 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
             FRec r = it.r;
             r.i0 = direct_centres_per_wave(it.h->nc);
             long long b = (it.h->nc + r.i0 - 1) / r.i0;
-            add(kind, p2q_bucket(it.h->p), r, b, b, 0, 64);
+            add(kind, p2q_bucket(*it.h), r, b, b, 0, 64);
         }
         break;
     case FK_M2QBXL:
@@ -2721,7 +2730,7 @@ hipError_t fused_plan(FBuf &fb, int kind, const std::vector<FItem> &items, std::
         }
         break;
     case FK_SMOOTH:
-        for (const auto &it : items) add(kind, 0, it.r, it.h->n_smooth, it.h->n_smooth, 0, 64);
+        for (const auto &it : items) add(kind, it.h->far, it.r, it.h->n_smooth, it.h->n_smooth, 0, 64);
         break;
     default:
         return hipErrorInvalidValue;
@@ -2792,24 +2801,26 @@ hipError_t fused_launch(const FLaunch &L, const unsigned char *dev, hipStream_t 
         break;
     case FK_P2QBXL:
         switch (L.variant) {
-        case 8: FL(kf_p2qbxl<8>); break;
-        case 12: FL(kf_p2qbxl<12>); break;
-        case 14: FL(kf_p2qbxl<14>); break;
-        case 16: FL(kf_p2qbxl<16>); break;
-        case 24: FL(kf_p2qbxl<24>); break;
-        case 32: FL(kf_p2qbxl<32>); break;
-        default: FL(kf_p2qbxl<40>); break;
+        case kFarBucket: FL(kf_p2qbxl<40, true>); break;
+        case 8: FL(kf_p2qbxl<8, false>); break;
+        case 12: FL(kf_p2qbxl<12, false>); break;
+        case 14: FL(kf_p2qbxl<14, false>); break;
+        case 16: FL(kf_p2qbxl<16, false>); break;
+        case 24: FL(kf_p2qbxl<24, false>); break;
+        case 32: FL(kf_p2qbxl<32, false>); break;
+        default: FL(kf_p2qbxl<40, false>); break;
         }
         break;
     case FK_P2QBXL_DIRECT:
         switch (L.variant) {
-        case 8: FL(kf_p2qbxl_direct<8>); break;
-        case 12: FL(kf_p2qbxl_direct<12>); break;
-        case 14: FL(kf_p2qbxl_direct<14>); break;
-        case 16: FL(kf_p2qbxl_direct<16>); break;
-        case 24: FL(kf_p2qbxl_direct<24>); break;
-        case 32: FL(kf_p2qbxl_direct<32>); break;
-        default: FL(kf_p2qbxl_direct<40>); break;
+        case kFarBucket: FL(kf_p2qbxl_direct<40, true>); break;
+        case 8: FL(kf_p2qbxl_direct<8, false>); break;
+        case 12: FL(kf_p2qbxl_direct<12, false>); break;
+        case 14: FL(kf_p2qbxl_direct<14, false>); break;
+        case 16: FL(kf_p2qbxl_direct<16, false>); break;
+        case 24: FL(kf_p2qbxl_direct<24, false>); break;
+        case 32: FL(kf_p2qbxl_direct<32, false>); break;
+        default: FL(kf_p2qbxl_direct<40, false>); break;
         }
         break;
     case FK_M2QBXL: FL(kf_m2qbxl); break;
@@ -2822,7 +2833,10 @@ hipError_t fused_launch(const FLaunch &L, const unsigned char *dev, hipStream_t 
         if (L.variant) FL(kf_eval<true>);
         else FL(kf_eval<false>);
         break;
-    case FK_SMOOTH: FL(kf_smooth); break;
+    case FK_SMOOTH:
+        if (L.variant) FL(kf_smooth<true>);
+        else FL(kf_smooth<false>);
+        break;
     default: return hipErrorInvalidValue;
     }
 #undef FL

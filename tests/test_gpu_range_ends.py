@@ -25,7 +25,7 @@ def _dev(a):
 # H_0 and H_1 at omega 2^k and targets at powers of two from one source at the
 # origin, so that x is exact: at centres (p = 0) and by the smooth rule.  As
 # between the forms of the ordinary range: 4e-15.
-def _hankel_at(ctx, which, bound, k):
+def _hankel_at(ctx, which, bound, k, direct=True):
     mp = pytest.importorskip("mpmath")
     from paper_1602_05301_amd import qbx
     omega, d = 2.0 ** k, 2.0 ** np.arange(-3, 4)
@@ -33,9 +33,14 @@ def _hankel_at(ctx, which, bound, k):
                         d, 0.0 * d, 1e-3 * d)
     tx = d if bound else -d
     tc = np.arange(d.size, dtype=np.int32) if bound else np.full(d.size, -1, dtype=np.int32)
-    geo = qbx.Geometry(ctx, pts, omega, 1e-10, tx, 0.0 * tx, tc, qbx.options(p=0, direct=True))
+    geo = qbx.Geometry(ctx, pts, omega, 1e-10, tx, 0.0 * tx, tc, qbx.options(p=0, direct=direct))
     sig = _dev(np.ones((1, 1), dtype=np.complex128))
-    u = geo.eval(sig if which == "S" else None, sig if which == "D" else None).cpu().numpy()[0]
+    sig = (sig if which == "S" else None, sig if which == "D" else None)
+    u = geo.eval(*sig).cpu().numpy()[0]
+    both = torch.empty((1, tx.size), dtype=torch.complex128, device="cuda:0")
+    ctx.eval_batch([geo], [sig[0]], [sig[1]], [both])
+    torch.cuda.synchronize()
+    assert np.array_equal(both.cpu().numpy()[0], u)
     n = 0 if which == "S" else 1
 
     def hankel(x):
@@ -60,12 +65,13 @@ def test_hankel_at_tiny_arguments(ctx, which, bound, k):
 
 
 # Arguments on both sides of 1e14, where the phase takes another reduction, and
-# far beyond.
+# far beyond, by the direct rule and (a tree of one box) by the near field.
+@pytest.mark.parametrize("direct", [True, False])
 @pytest.mark.parametrize("bound", [True, False])
 @pytest.mark.parametrize("which", ["S", "D"])
 @pytest.mark.parametrize("k", [45, 47, 52, 60, 300])
-def test_hankel_at_huge_arguments(ctx, which, bound, k):
-    _hankel_at(ctx, which, bound, k)
+def test_hankel_at_huge_arguments(ctx, which, bound, k, direct):
+    _hankel_at(ctx, which, bound, k, direct)
 
 
 # L2QBXL at leaf orders around the bounds where its staging changes: at p = 14
