@@ -59,6 +59,11 @@ struct QbxLane {
     hipEvent_t ev_fork = nullptr, ev_x = nullptr, ev_q = nullptr, ev_m = nullptr;
 };
 
+// A device block; q null: none.
+struct TmpBlock {
+    void *q = nullptr;
+    size_t n = 0;
+};
 constexpr size_t kTmpKeep = 2, kTmpKeepBytes = size_t(16) << 20;
 
 struct qbx_ctx_s {
@@ -88,10 +93,10 @@ struct qbx_ctx_s {
     // workspace of qbx_krylov_dot (partial sums), grown on demand
     cd *kw = nullptr;
     size_t kw_cap = 0;
-    // idle device blocks of the area-query calls (DevTmp), at most kTmpKeep of
-    // at most kTmpKeepBytes; freed with the context
+    // idle device blocks of the area-query calls (DevTmp): the kTmpKeep largest
+    // seen of at most kTmpKeepBytes each; freed with the context
     std::mutex tmp_mu;
-    std::vector<std::pair<void *, size_t>> tmp_free;
+    TmpBlock tmp_free[kTmpKeep];
     // the thread inside a call on this context (nested calls of that thread
     // count in depth), and the message of the last failed call
     std::atomic<std::thread::id> owner{};
@@ -1715,7 +1720,8 @@ void ctx_release(qbx_ctx_s *ctx)
     if (ctx->ev_in) (void)hipEventDestroy(ctx->ev_in);
     if (ctx->ev_out) (void)hipEventDestroy(ctx->ev_out);
     if (ctx->kw) (void)hipFree(ctx->kw);
-    for (auto &b : ctx->tmp_free) (void)hipFree(b.first);
+    for (auto &b : ctx->tmp_free)
+        if (b.q) (void)hipFree(b.q);
     delete ctx;
 }
 
@@ -2425,44 +2431,56 @@ qbx_status qbx_geom_graph(qbx_geom G, int32_t enable)
 // ---- area queries and association on the device ---------------------------
 namespace {
 
-// Temporary device buffers of one call.  A call that has waited for its
-// stream leaves them to the next call on the context, within bounds (each
-// allocation and release costs more than the small kernels between).
+// Temporary device buffers of one call, kTmpKeep at most.  A call that has
+// waited for its stream leaves them to the next calls on the context, within
+// bounds (each allocation and release costs more than the small kernels
+// between): a block takes a free place or the smallest kept one's, so that what
+// is kept does not depend on which calls came first.
 struct DevTmp {
     qbx_ctx_s *c;
-    std::vector<std::pair<void *, size_t>> blocks;
+    TmpBlock blocks[kTmpKeep];
+    size_t used = 0;
     hipError_t err = hipSuccess;
     bool idle = false;                  // the stream that used the blocks has been waited for
     explicit DevTmp(qbx_ctx_s *ctx) : c(ctx) {}
     unsigned char *block(size_t n)
     {
-        n = std::max<size_t>(n, 256);
-        {
-            std::lock_guard<std::mutex> lk(c->tmp_mu);
-            for (size_t i = 0; i < c->tmp_free.size(); ++i)
-                if (c->tmp_free[i].second >= n) {
-                    blocks.push_back(c->tmp_free[i]);
-                    c->tmp_free.erase(c->tmp_free.begin() + (long)i);
-                    return static_cast<unsigned char *>(blocks.back().first);
-                }
+        if (err != hipSuccess || used == kTmpKeep) {
+            if (err == hipSuccess) err = hipErrorOutOfMemory;
+            return nullptr;
         }
-        void *q = nullptr;
-        if (err == hipSuccess) err = hipMalloc(&q, n);
-        if (err != hipSuccess) return nullptr;
-        blocks.push_back({q, n});
-        return static_cast<unsigned char *>(q);
+        n = std::max<size_t>(n, 256);
+        TmpBlock &b = blocks[used];
+        {
+            // the smallest kept block that is large enough
+            std::lock_guard<std::mutex> lk(c->tmp_mu);
+            TmpBlock *fit = nullptr;
+            for (auto &f : c->tmp_free)
+                if (f.q && f.n >= n && (!fit || f.n < fit->n)) fit = &f;
+            if (fit) std::swap(b, *fit);
+        }
+        if (!b.q) {
+            err = hipMalloc(&b.q, n);
+            if (err != hipSuccess) {
+                b.q = nullptr;
+                return nullptr;
+            }
+            b.n = n;
+        }
+        ++used;
+        return static_cast<unsigned char *>(b.q);
     }
     ~DevTmp()
     {
         for (auto &b : blocks) {
-            {
+            if (b.q && idle && b.n <= kTmpKeepBytes) {
                 std::lock_guard<std::mutex> lk(c->tmp_mu);
-                if (idle && b.second <= kTmpKeepBytes && c->tmp_free.size() < kTmpKeep) {
-                    c->tmp_free.push_back(b);
-                    continue;
-                }
+                TmpBlock *least = &c->tmp_free[0];
+                for (auto &f : c->tmp_free)
+                    if (f.n < least->n) least = &f;
+                if (least->n < b.n) std::swap(b, *least);
             }
-            (void)hipFree(b.first);
+            if (b.q) (void)hipFree(b.q);
         }
     }
     DevTmp(const DevTmp &) = delete;

@@ -176,3 +176,37 @@ def test_evaluation_far_from_the_centre(ctx, p):
     ctx.eval_batch([geo], [sig], [None], [both])
     torch.cuda.synchronize()
     assert np.array_equal(both.cpu().numpy(), u)
+
+
+# The kept blocks of the query calls: small calls first, then larger ones.  The
+# largest blocks are the ones kept (the driver's free memory falls by them once
+# and stays), and no more than two of at most 16 MiB each.
+def test_query_blocks_are_kept_in_any_order(ctx):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(40, 16, lobes=5, amp=0.3)
+
+    def geometry(c):
+        return qbx.Geometry(c, g, 5.0, 1e-8, g.sx, g.sy, np.arange(g.n, dtype=np.int32), qbx.options(p=8))
+    r = np.random.default_rng(3)
+    n = 1000000
+    x, y, rad = _dev(r.uniform(-1.4, 1.4, n)), _dev(r.uniform(-1.4, 1.4, n)), _dev(np.full(n, -1.0))
+    free = lambda: torch.cuda.mem_get_info(0)[0]
+
+    def query(geo, m):
+        geo.area_query(x[:m], y[:m], rad[:m])
+        torch.cuda.synchronize()
+        return free()
+    sizes = (10, 20000, n, n, 700000, n)
+    warm = geometry(qbx.Context(0))               # torch's own buffers of these sizes
+    for m in sizes:
+        query(warm, m)
+    c = qbx.Context(0)
+    geo = geometry(c)
+    geo.points_near("sources", x[:10], y[:10], rad[:10])
+    query(geo, 10)
+    f0 = query(geo, 20000)
+    f1 = query(geo, n)
+    assert f0 - f1 >= 3 * n                       # n counts of four bytes, less what was freed
+    assert query(geo, n) == f1 and query(geo, 700000) == f1 and query(geo, n) == f1
+    geo.associate(x[:1000], y[:1000])
+    assert f0 - free() <= 2 * (16 << 20)
