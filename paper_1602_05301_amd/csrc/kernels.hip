@@ -329,10 +329,10 @@ __device__ __forceinline__ int xcd_contiguous(int b, int n)
     return (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + i;
 }
 
-// V-list part of the downward pass: local = X-list part (already in loc)
-// + the box's V-list contributions in list order.  Block bid.x takes box
-// level_start[l] + bid.x, so a launch of nb - level_start[2] blocks from
-// l = 2 covers every level at once.  L2L, given no V-list rows, then adds its
+// V-list part of the downward pass: local = X-list part (already in loc, where
+// the box has an X list) + the box's V-list contributions in list order.  Block
+// bid.x takes box level_start[l] + bid.x, so a launch of all boxes from l = 0
+// covers every level at once.  L2L, given no V-list rows, then adds its
 // translation to these sums: the same terms in the same order as when its
 // epilogue summed the rows, with one bandwidth-bound launch in place of the
 // epilogues' loads in every latency-bound L2L level.
@@ -344,8 +344,9 @@ __device__ __forceinline__ void down_body(const DevGeom &g, int nd, int l, const
     int v0 = g.V_start[b], nv = g.V_start[b + 1] - v0;
     const bool hasx = g.X_start[b + 1] > g.X_start[b];
     if (nv == 0 && hasx) return;
-    // the box's V-list rows follow each other, n * nd apart
-    const cd *vr = vy + g.vy_off[v0] * nd;
+    // the box's V-list rows follow each other, n * nd apart (v0 is past the end
+    // of the list for boxes behind its last entry)
+    const cd *vr = nv > 0 ? vy + g.vy_off[v0] * nd : vy;
     long long vs = (long long)n * nd;
     for (int i = threadIdx.x; i < nd * n; i += blockDim.x) {
         cd acc = hasx ? out[i] : mk(0.0, 0.0);

@@ -219,9 +219,9 @@ hipError_t launch_m2l_mfma(const DevGeom &g, int nd, const M2LTile *tiles, int n
                            int Pdirect, int Pstaged, int nw, const cd *mp, cd *vy, hipStream_t s);
 // Largest order whose M2L columns the staged kernel holds in LDS.
 int m2l_staged_pmax();
-// V-list sums of the nbox boxes from the first of level 2 on (every level
-// >= 2) in one launch, nd (1-4) densities; launch_l2l_mfma with vy = null
-// then leaves them out of its epilogue.
+// V-list sums of the first nbox boxes (all of them: every local is written, with
+// or without lists) in one launch, nd (1-4) densities; launch_l2l_mfma with
+// vy = null then leaves them out of its epilogue.
 hipError_t launch_down_all(const DevGeom &g, int nd, int nbox, const cd *vy, cd *loc, hipStream_t s);
 // X-list P2L into the locals of the listed boxes.
 hipError_t launch_p2l_x(const DevGeom &g, int nd, const int *list, int n, int Pmax, const cd *qs,

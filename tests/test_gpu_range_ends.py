@@ -210,3 +210,32 @@ def test_query_blocks_are_kept_in_any_order(ctx):
     assert query(geo, n) == f1 and query(geo, 700000) == f1 and query(geo, n) == f1
     geo.associate(x[:1000], y[:1000])
     assert f0 - free() <= 2 * (16 << 20)
+
+
+# Boxes with neither a V nor an X list behind the last V-list entry (two small
+# curves far apart: chains of single children below level 2): their locals are
+# zero plus the parent's, with no row to look up.  eps is 1e-10, ten times that
+# in l2.
+@pytest.mark.parametrize("nd", [1, 3])
+def test_boxes_behind_the_last_v_list_entry(ctx, nd):
+    from paper_1602_05301_amd import qbx
+    g = inputs.concat([inputs.star(4, 16, lobes=3, amp=0.1, radius=0.02, center=(0.9, 0.87)),
+                       inputs.star(4, 16, lobes=3, amp=0.1, radius=0.02, center=(-0.91, -0.88))])
+    tc = np.arange(g.n, dtype=np.int32)
+    opts = qbx.options(p=8, leaf_max=48)
+    plan = qbx.Plan(g, 5.0, 1e-10, g.sx, g.sy, tc, opts)
+    v, x = plan.list(1)[0], plan.list(3)[0]
+    behind = (v[:-1] == v[-1]) & (x[1:] == x[:-1])
+    assert v[-1] > 0 and behind.sum() > 8
+    r = np.random.default_rng(nd)
+    ss, sd = inputs.complex_gaussian(r, (nd, g.n)), inputs.complex_gaussian(r, (nd, g.n))
+    ref = oracle.direct_qbx(5.0, 8, g, g.sx, g.sy, ss, sd, tgt_ctr=tc)
+    geo = qbx.Geometry(ctx, g, 5.0, 1e-10, g.sx, g.sy, tc, opts)
+    u = geo.eval(_dev(ss), _dev(sd))
+    both = torch.empty_like(u)
+    ctx.eval_batch([geo], [_dev(ss)], [_dev(sd)], [both])
+    torch.cuda.synchronize()
+    assert torch.equal(both, u)
+    err = np.linalg.norm(u.cpu().numpy() - ref) / np.linalg.norm(ref)
+    print(f"nd {nd}: {err:.2e}", flush=True)
+    assert err <= 1e-9
