@@ -288,10 +288,22 @@ struct WorkList {
 constexpr long long kP2qLanePairs = 8;
 // Where items of twice that are still 16 per CU, many follow each other on every
 // CU and the few that outlast the rest matter less than each item's staging and
-// reduction: curves with leaves of 64 (110000 nodes) 822 us a pass with 8 and
-// 787 with 16, 200000 nodes 1770 and 1753.  Below, the launch lasts as long as
-// its longest items: 32768 nodes (13 per CU) 353 and 361.
-constexpr long long kP2qManyItems = 16 * 256;
+// reduction.  Passes with 8 and with 16 pairs a lane, by items of 16 per CU:
+// leaves of 64, 16.3 456 and 440 us, 19.3 509 and 492, 28 693 and 663, 39 906 and
+// 866 (p = 14), 16.5 397 and 382 (p = 10); leaves of 32, which rarely need the
+// split, 17.8 489 and 494, 24 618 and 618, 48 1097 and 1100.  Below, the launch
+// lasts as long as its longest items, and what either gains depends on the
+// curve: 6.8 266 and 269, 10 295 and 308, 12 369 and 373, 14 404 and 392.
+constexpr long long kP2qItemsPerCu = 16;
+
+// Compute units of the context's device (256 for a plan without one).
+int device_cus(const qbx_ctx_s *ctx)
+{
+    int n = 0;
+    if (ctx && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
+        (void)hipGetLastError();
+    return n > 0 ? n : 256;
+}
 
 }  // namespace
 
@@ -893,10 +905,15 @@ qbx_status upload(qbx_geom_s *G)
             while (ng < nc && lane_pairs((nc + ng - 1) / ng, nsrc) > limit) ++ng;
             return ng;
         };
-        long long many = 0;
-        for (int b = 0; b < nb && many < kP2qManyItems; ++b)
-            if (pl.leaf[b] && has_ctr(b)) many += groups(b, near_sources(b), 2 * kP2qLanePairs);
-        const long long lane_limit = many < kP2qManyItems ? kP2qLanePairs : 2 * kP2qLanePairs;
+        const long long many = kP2qItemsPerCu * device_cus(G->ctx);
+        long long larger = 0, smaller = 0;             // items of twice kP2qLanePairs and of one
+        for (int b = 0; b < nb; ++b)
+            if (pl.leaf[b] && has_ctr(b)) {
+                long long n = near_sources(b);
+                larger += groups(b, n, 2 * kP2qLanePairs);
+                smaller += groups(b, n, kP2qLanePairs);
+            }
+        const long long lane_limit = larger < many ? kP2qLanePairs : 2 * kP2qLanePairs;
         std::vector<int32_t> qidx;
         std::vector<std::array<int32_t, 4>> qitems;
         std::vector<long long> qwork;
@@ -921,6 +938,8 @@ qbx_status upload(qbx_geom_s *G)
         std::vector<int32_t> qflat;
         for (int i : qord) qflat.insert(qflat.end(), qitems[i].begin(), qitems[i].end());
         G->qbx.n = (int)qord.size();
+        // room for either, so that the size needs no device
+        qflat.resize(4 * (size_t)std::max(smaller, larger), 0);
         G->qbx.d = ar.upload(qflat);
         g.qsrc_idx = ar.upload(qidx);
         // sources of all X-list boxes of every box of the X-list P2L list, in list order

@@ -239,3 +239,52 @@ def test_boxes_behind_the_last_v_list_entry(ctx, nd):
     err = np.linalg.norm(u.cpu().numpy() - ref) / np.linalg.norm(ref)
     print(f"nd {nd}: {err:.2e}", flush=True)
     assert err <= 1e-9
+
+
+# The near field's item sizes on both sides of their rule: 16 pairs a lane where
+# such items are 16 per CU, 8 below.  The items are counted from the plan (near
+# lists of the U lists alone, w_direct = 0), as the launch counts them; then the
+# FMM against the direct mode at every target, and a batch with a small geometry
+# against the call alone.  eps is 1e-8, ten times that in l2.
+def _items(plan, limit):
+    box = plan.boxes()
+    start, idx = plan.list(0)
+    total = 0
+    for b in np.nonzero((box["leaf"] > 0) & (box["nctr"] > 0))[0]:
+        nc, ns, ng = int(box["nctr"][b]), int(box["nsrc"][idx[start[b]:start[b + 1]]].sum()), 1
+
+        def pairs(n):
+            cg = max(1, min(n, 64))
+            parts = 128 // cg
+            return -(-ns // parts) * -(-n // cg)
+        while ng < nc and pairs(-(-nc // ng)) > limit:
+            ng += 1
+        total += ng
+    return total
+
+
+@pytest.mark.parametrize("panels,many", [(2800, False), (3800, True)])
+def test_near_field_item_rule(ctx, panels, many):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(panels, 16, lobes=7, amp=0.3)
+    tc = np.arange(g.n, dtype=np.int32)
+    opts = qbx.options(p=10, leaf_max=64, w_direct=0)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    larger = _items(qbx.Plan(g, 40.0, 1e-8, g.sx, g.sy, tc, opts), 16)
+    print(f"panels {panels}: {larger / cus:.1f} items per CU", flush=True)
+    assert (larger >= 16 * cus) == many and 12 * cus < larger < 20 * cus
+    r = np.random.default_rng(panels)
+    sig = _dev(inputs.complex_gaussian(r, (1, g.n)))
+    geo = qbx.Geometry(ctx, g, 40.0, 1e-8, g.sx, g.sy, tc, opts)
+    u = geo.eval(sig, sig)
+    ref = qbx.Geometry(ctx, g, 40.0, 1e-8, g.sx, g.sy, tc, qbx.options(p=10, direct=True)).eval(sig, sig)
+    err = float(torch.linalg.norm(u - ref) / torch.linalg.norm(ref))
+    print(f"panels {panels}: {err:.2e}", flush=True)
+    assert err <= 1e-7
+    s = inputs.star(40, 16, lobes=3, amp=0.3)
+    small = qbx.Geometry(ctx, s, 10.0, 1e-8, s.sx, s.sy, np.arange(s.n, dtype=np.int32), opts)
+    ssig = sig[:, :s.n].contiguous()
+    both = [torch.empty_like(ssig), torch.empty_like(u)]
+    ctx.eval_batch([small, geo], [ssig, sig], [ssig, sig], both)
+    torch.cuda.synchronize()
+    assert torch.equal(both[1], u) and torch.equal(both[0], small.eval(ssig, ssig))
