@@ -2522,6 +2522,7 @@ AQTree aq_tree(const qbx_geom_s *G)
     t.leaf = G->g.leaf;
     t.child4 = G->g.child4;
     t.R0 = G->pl.R0;
+    t.stack = aq_stack(G->pl.nlev);
     return t;
 }
 

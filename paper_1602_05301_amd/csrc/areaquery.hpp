@@ -16,7 +16,10 @@ struct AQTree {
     const double *bcx, *bcy;
     const int *blev, *leaf, *child4;
     double R0;
+    int stack;      // entries a traversal may need: aq_stack(levels)
 };
+
+inline int aq_stack(int nlev) { return 9 + 3 * (nlev > 1 ? nlev - 1 : 0); }
 
 // Result lists are keyed by region: 5b + 4 for leaf b, 5b + q for the empty
 // quadrant q of a box b that has children (the tree leaves out children

@@ -288,3 +288,40 @@ def test_near_field_item_rule(ctx, panels, many):
     ctx.eval_batch([small, geo], [ssig, sig], [ssig, sig], both)
     torch.cuda.synchronize()
     assert torch.equal(both[1], u) and torch.equal(both[0], small.eval(ssig, ssig))
+
+
+# Area queries and disk tests on the deepest tree (two coincident sources in
+# leaves of one point: 31 levels), from squares about them and about other points,
+# against every leaf of the plan.  The stack's bound is 9 + 3 per level.
+def test_area_queries_on_the_deepest_tree(ctx):
+    from paper_1602_05301_amd import qbx
+    g = inputs.star(8, 16, lobes=3, amp=0.3)
+    dup = np.array([g.sx[5], g.sx[77]]), np.array([g.sy[5], g.sy[77]])
+    cat = lambda a, b: np.concatenate([a, b])
+    pts = inputs.Points(cat(g.sx, dup[0]), cat(g.sy, dup[1]), cat(g.w, g.w[:2]), cat(g.nx, g.nx[:2]),
+                        cat(g.ny, g.ny[:2]), cat(g.h, g.h[:2]), g.cx, g.cy, g.cr)
+    tc = np.arange(g.n, dtype=np.int32)
+    opts = qbx.options(p=2, direct=True, leaf_max=1, level_restrict=False)
+    plan = qbx.Plan(pts, 1.0, 1e-6, g.sx, g.sy, tc, opts)
+    box = plan.boxes()
+    assert plan.stats()["n_levels"] == 31
+    R0 = plan.stats()["root_radius"]
+    leaf = np.nonzero(box["leaf"])[0]
+    rb = np.ldexp(R0, -box["level"][leaf])
+    bx, by = -R0 + (2 * box["ix"][leaf] + 1) * rb, -R0 + (2 * box["iy"][leaf] + 1) * rb
+    r = np.random.default_rng(9)
+    n = 600
+    at = r.integers(0, pts.sx.size, n)
+    at[:200:2], at[1:200:2] = 5, pts.sx.size - 1
+    rad = 10.0 ** r.uniform(-11, 0.5, n)
+    x, y = pts.sx[at] + 0.3 * rad, pts.sy[at] - 0.2 * rad
+    geo = qbx.Geometry(ctx, pts, 1.0, 1e-6, g.sx, g.sy, tc, opts)
+    start, leaves = (a.cpu().numpy() for a in geo.area_query(_dev(x), _dev(y), _dev(rad)))
+    near = geo.points_near("sources", _dev(x), _dev(y), _dev(rad)).cpu().numpy()
+    for i in range(n):
+        gap = np.maximum(abs(bx - x[i]), abs(by - y[i])) - rb - rad[i]
+        tol = 1e-14 * (R0 + rad[i])
+        got = set(leaves[start[i]:start[i + 1]].tolist())
+        assert set(leaf[gap < -tol].tolist()) <= got <= set(leaf[gap <= tol].tolist()), i
+        d2 = (pts.sx - x[i]) ** 2 + (pts.sy - y[i]) ** 2
+        assert near[i] == (d2 <= rad[i] ** 2).any()
