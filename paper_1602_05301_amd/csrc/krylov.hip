@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(KP_THREADS) k_upsample(long long n_panels, int
     }
 }
 
-// The same for panels too long for LDS: one thread per fine node.
+// The same for panels too long for LDS, or too short for its staging: one thread per fine node.
 __global__ void k_upsample_long(long long n_panels, int q, int qs, const double *L, cd alpha, const cd *x, cd *ys,
                                 cd *yd)
 {
@@ -229,9 +229,13 @@ hipError_t launch_upsample(long long n_panels, int q, int qs, const double *L, c
 {
     long long t = n_panels * qs;
     if (t <= 0) return hipSuccess;
-    // LDS of the staged form; sizes past 64 KiB (q and qs about 80) read through the caches
+    // LDS of the staged form; sizes past 64 KiB (q and qs about 80) read through
+    // the caches, and so do panels and rows so short that staging a block's takes
+    // longer than its few sums: 200000 panels, 4 to 4 nodes 9.6 us a call and 14.5
+    // staged, 1 to 4 8.2 and 13.3, 16 to 1 22.5 and 23.5, 64 to 2 68 and 82; but 8
+    // to 8 29 and 18, 16 to 4 39 and 23, 64 to 4 123 and 77.
     size_t lds = sizeof(double) * (2 * (size_t)KP_PANELS * q + (size_t)qs * (q + 1));
-    if (lds <= 64 * 1024)
+    if (lds <= 64 * 1024 && q >= 8 && qs >= 4)
         k_upsample<<<(unsigned)((n_panels + KP_PANELS - 1) / KP_PANELS), KP_THREADS, lds, s>>>(n_panels, q, qs, L, alpha, x, ys, yd);
     else
         k_upsample_long<<<(unsigned)((t + 255) / 256), 256, 0, s>>>(n_panels, q, qs, L, alpha, x, ys, yd);

@@ -325,3 +325,17 @@ def test_area_queries_on_the_deepest_tree(ctx):
         assert set(leaf[gap < -tol].tolist()) <= got <= set(leaf[gap <= tol].tolist()), i
         d2 = (pts.sx - x[i]) ** 2 + (pts.sy - y[i]) ** 2
         assert near[i] == (d2 <= rad[i] ** 2).any()
+
+
+# Panel interpolation on both sides of the staging's lower bounds (panels of 8
+# nodes, 4 rows), panel counts around a block's: sums of q products of
+# unit-variance entries, 1e-12 as in the tests of longer panels.
+@pytest.mark.parametrize("panels,q,qs", [(1, 7, 4), (9, 8, 3), (7, 8, 4), (17, 7, 40), (300, 64, 2), (300, 2, 2)])
+def test_upsample_of_short_panels(ctx, panels, q, qs):
+    r = np.random.default_rng(panels + q)
+    L, x = r.standard_normal((qs, q)), inputs.complex_gaussian(r, (panels * q,))
+    ys, yd = _dev(np.zeros(panels * qs, dtype=np.complex128)), _dev(np.zeros(panels * qs, dtype=np.complex128))
+    ctx.upsample(_dev(L), q, qs, _dev(x), 2.0 - 1.0j, ys=ys, yd=yd)
+    ref = (x.reshape(panels, q) @ L.T).ravel()
+    assert np.abs(yd.cpu().numpy() - ref).max() <= 1e-12
+    assert np.abs(ys.cpu().numpy() - (2.0 - 1.0j) * ref).max() <= 1e-11
