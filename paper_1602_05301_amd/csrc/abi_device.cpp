@@ -471,7 +471,7 @@ qbx_status upload(qbx_geom_s *G)
             continue;
         }
         double x = pl.omega * std::hypot(pl.tx[m] - pl.cx[v], pl.ty[m] - pl.cy[v]);
-        if (x > kEvalUpX || (x < kEvalLeadX && x != 0.0)) g.eval_ends = 1;
+        if (x > kEvalUpX || (x != 0.0 && (x < kEvalLeadX || pl.p == 0))) g.eval_ends = 1;
     }
     // distances are at most the diameter of the origin-centred disk of all points
     double rmax_all = 0.0;

@@ -1877,12 +1877,18 @@ __global__ void __launch_bounds__(L2Q_THREADS) k_l2qbxl(DevGeom g, int nd, const
 // in one loop: 19 us for 512 targets, 15 for 32768 (p = 14), 39 for
 // four densities of them, 25 for 200000 FP64 sources; now 9.6,
 // 10.6, 21.3, 24.6.
-// ENDS: some target is nearer to its centre than kEvalLeadX or farther than
-// kEvalUpX (in 1/omega).  Near, J_n = (x/2)^n / n! to rounding, and the
+// The normalised J_0 is taken from the sum where that is the smaller part, so
+// that it is as close as the library's: errors of whole expansions, p = 14, in
+// 1e-16 of their terms' root sum of squares, with j0 and j1 and now: 1.1 and 1.1
+// below x = 0.1, 2.2 and 2.3 to 1, 3.3 and 3.6 to 5, 7.8 and 7.1 to 15, 95 and 87
+// at 30 to 60.
+// ENDS: p = 0, or some target is nearer to its centre than kEvalLeadX or farther
+// than kEvalUpX (in 1/omega).  Near, J_n = (x/2)^n / n! to rounding, and the
 // recurrence would leave the exponent range within a step or two at the smallest
-// x; far, J_n comes upward from J_0 and J_1, stable for n < x, as the downward
-// recurrence takes x steps, rounds at each, and its start is an int.  A form of
-// its own, so that the common one makes no call.
+// x; far, J_n comes upward from the library's J_0 and J_1, stable for n < x, as
+// the downward recurrence takes x steps, rounds at each, and its start is an int;
+// for p = 0 J_0 is all there is.  A form of its own, as the library's code is
+// longer than all the rest.
 // ---------------------------------------------------------------------------
 constexpr int EVAL_THREADS = 64;   // few targets then still reach every CU
 
@@ -1904,9 +1910,8 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
     cd v = rho > 0.0 ? mk(dx / rho, -dy / rho) : mk(1.0, 0.0);   // e^{-i theta}
     long long o = g.tgt_out ? (long long)g.tgt_out[m] : (long long)m;
     double *J = lds_raw + threadIdx.x;
-    double s = 1.0;
+    double s = 1.0, jz = 1.0;                                    // J_n = s J[n], J_0 = jz
     int top = 0;                                                 // at rho = 0 only l = 0 counts
-    J[0] = 1.0;
     if (ENDS && x != 0.0 && x < kEvalLeadX) {
         top = p;
         double f = 1.0;
@@ -1914,12 +1919,10 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
             f *= 0.5 * x / n;
             J[n * EVAL_THREADS] = f;
         }
-    } else if (ENDS && x > kEvalUpX) {
+    } else if (ENDS && (x > kEvalUpX || (p == 0 && x != 0.0))) {
         top = p;
-        cd h0, h1;
-        hankel01<true>(x, 1.0 / x, h0, h1);
-        double a = h0.x, b = h1.x;
-        J[0] = a;
+        double a = j0(x), b = p > 0 ? j1(x) : 0.0;
+        jz = a;
         for (int n = 1; n <= p; ++n) {
             J[n * EVAL_THREADS] = b;
             double c = fma(2.0 * n / x, b, -a);
@@ -1941,12 +1944,13 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
                 for (int k = n; k <= p; ++k) J[k * EVAL_THREADS] *= 1e-250;
             }
         }
-        J[0] = f;
+        // J_0 from the sum while that is the smaller part
         s = 1.0 / fma(2.0, sum, f);
+        jz = x < 1.5 ? fma(-2.0 * s, sum, 1.0) : s * f;
     }
     for (int d = 0; d < nd; ++d) {
         const cd *a = coef + (long long)d * nq * nc + i + (long long)p * nc;
-        cd S = J[0] * a[0];
+        cd S = mk(0.0, 0.0);
         cd ep = v;                                               // e^{-i n theta}
 #pragma unroll 4
         for (int n = 1; n <= top; ++n) {
@@ -1956,7 +1960,7 @@ __device__ __forceinline__ void qbx_eval_body(const DevGeom &g, int nd, const cd
             S = S + J[n * EVAL_THREADS] * (t + tm);
             ep = ep * v;
         }
-        u[(long long)d * g.u_stride + o] = s * S;
+        u[(long long)d * g.u_stride + o] = mk(fma(s, S.x, jz * a[0].x), fma(s, S.y, jz * a[0].y));
     }
 }
 

@@ -42,7 +42,7 @@ struct DevGeom {
     int ns, nc, nt, nb, nlev, p, n_smooth;
     int max_leaf_ctr;                          // most centres in one leaf
     int far;                                   // omega times a distance may be beyond kPhaseMax
-    int eval_ends;                             // a bound target with omega |t - c| beyond one of these bounds
+    int eval_ends;                             // p = 0, or a bound target with omega |t - c| beyond one of these bounds
     double omega;
     const QBX_G double *sx, *sy, *sw, *snx, *sny;   // sorted sources
     const QBX_G int *src_perm;                       // sorted -> user source index

@@ -339,3 +339,24 @@ def test_upsample_of_short_panels(ctx, panels, q, qs):
     ref = (x.reshape(panels, q) @ L.T).ravel()
     assert np.abs(yd.cpu().numpy() - ref).max() <= 1e-12
     assert np.abs(ys.cpu().numpy() - (2.0 - 1.0j) * ref).max() <= 1e-11
+
+
+# Expansions of order 0 away from their centres: the value is the coefficient
+# times J_0, as close as the library's j0 (an ulp or two of its envelope
+# sqrt(2 / (pi x)), and the product's rounding): 1e-15 of it.
+def test_order_zero_takes_no_sum(ctx):
+    mp = pytest.importorskip("mpmath")
+    from paper_1602_05301_amd import qbx
+    x = np.concatenate([np.linspace(1.0, 40.0, 157), np.linspace(40.3, 99.7, 98)])
+    pts = inputs.Points(np.array([40.0]), np.zeros(1), np.ones(1), np.ones(1), np.zeros(1), np.ones(1),
+                        np.zeros(1), np.zeros(1), np.ones(1))
+    geo = qbx.Geometry(ctx, pts, 1.0, 1e-10, x, 0.0 * x, np.zeros(x.size, dtype=np.int32),
+                       qbx.options(p=0, direct=True))
+    sig = _dev(np.full((1, 1), 0.75 - 0.5j))
+    u, coef = (a.cpu().numpy() for a in geo.eval(sig, None, coef=True))
+    with mp.workdps(40):
+        J = np.array([float(mp.besselj(0, mp.mpf(float(v)))) for v in x])
+    a = coef.reshape(1)[0]
+    err = np.abs(u[0] - a * J) / (np.abs(a) * np.sqrt(2 / (np.pi * x)))
+    print(f"p 0: {err.max():.2e} at x = {x[err.argmax()]:g}", flush=True)
+    assert err.max() <= 1e-15
