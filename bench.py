@@ -118,14 +118,16 @@ def m2l_algorithmic_bytes(plan, n_dens, far_fp32=False):
     """HBM bytes M2L must move at the least (Stage 4): each (level, rotation
     orbit) translation matrix read once, the multipole of every V-list source
     box read once and the V-list sum of every target box written once.
-    `pair_rows` is what this design writes instead of the sums: one row per
-    V-list pair, summed in list order by the downward pass."""
+    `tables` are the dense matrices; the library stores and reads the entries
+    that count for a row, the share that `dense_mfma_flops` gives against the
+    executed operations.  `pair_rows` is what this design writes instead of the
+    sums: one row per V-list pair, summed in list order by the downward pass."""
     st = plan.stats()
     bx = plan.boxes()
     P = plan.orders()
     vs, vi = plan.list(1)
     lev, ix, iy = bx["level"], bx["ix"].astype(np.int64), bx["iy"].astype(np.int64)
-    groups, srcs, tgts = set(), set(), set()
+    groups, srcs, tgts = {}, set(), set()
     rows = 0
     for b in range(st["n_boxes"]):
         rows += (vs[b + 1] - vs[b]) * (2 * int(P[lev[b]]) + 1)
@@ -133,33 +135,38 @@ def m2l_algorithmic_bytes(plan, n_dens, far_fp32=False):
             dx, dy, r = int(ix[v] - ix[b]), int(iy[v] - iy[b]), 0
             while not (dx > 0 and dy >= 0):          # quarter turns to the orbit representative
                 dx, dy, r = dy, -dx, r + 1
-            groups.add((int(lev[b]), dx, dy))
+            groups[int(lev[b]), dx, dy] = groups.get((int(lev[b]), dx, dy), 0) + 1
             srcs.add(int(v))
             tgts.add(b)
     n = lambda b: 2 * int(P[lev[b]]) + 1
     tab = (8 if far_fp32 else 16) * sum((2 * int(P[l]) + 1) ** 2 for l, _, _ in groups)
     vec = (8 if far_fp32 else 16) * n_dens
-    return {"tables": tab, "multipoles": vec * sum(n(b) for b in srcs),
+    # what the matrix cores would execute with dense tables: three real products
+    # of 16x16x4 blocks, 16 columns a tile
+    dense = sum(-(-c * n_dens // 16) * -(-(2 * int(P[l]) + 1) // 16) * -(-(2 * int(P[l]) + 1) // 4) * 3 * 2048
+                for (l, _, _), c in groups.items())
+    return {"tables": tab, "dense_mfma_flops": dense, "multipoles": vec * sum(n(b) for b in srcs),
             "locals": 16 * n_dens * sum(n(b) for b in tgts), "pair_rows": vec * int(rows)}
 
 
-def measured_traffic(kname):
-    """HBM bytes per launch of a kernel from the committed rocprofv3
-    FETCH_SIZE/WRITE_SIZE summary (copy-calibrated), or None when there is
-    none or the kernel source has changed since the counters were taken."""
+def measured(kname):
+    """A kernel's committed rocprofv3 counters per launch of the default workload:
+    HBM bytes (FETCH_SIZE/WRITE_SIZE, copy-calibrated) and the FP64 operations that
+    the matrix cores executed, or {} when there are none or the kernel source has
+    changed since the counters were taken."""
     import hashlib
     if not kname or not os.path.exists(TRAFFIC_FILE):
-        return None
+        return {}
     with open(TRAFFIC_FILE) as f:
         doc = json.load(f)
     src = os.path.join(ROOT, "paper_1602_05301_amd", "csrc", "kernels.hip")
     with open(src, "rb") as f:
         if hashlib.sha256(f.read()).hexdigest() != doc.get("kernels_source_sha256"):
-            return None
+            return {}
     for k, v in doc.get("kernels", {}).items():
         if k == kname or k.startswith(kname + "<"):
-            return v["hbm_bytes_per_dispatch"]
-    return None
+            return v
+    return {}
 
 
 def _oracle_rel(g, omega, p, ss, sd, got, pick):
@@ -453,21 +460,32 @@ def main(argv=None):
 
     ms_step = elapsed / args.steps * 1e3
     value = g.n * wl.n_dens * args.steps / elapsed
+    default_wl = (args.eps, args.p, p_add, args.n_dens, args.far_fp32) == (1e-10, 14, inputs.STAR32K_P_ADD, 1, False)
+
     def stage_roof(st):
-        # work counts the dense operators; the translations and L2QBXL multiply
-        # only the entries that count, about half, so their rate here is the
-        # operator's, not the matrix cores'
+        # work counts the dense operators.  The translations and L2QBXL multiply
+        # only the entries that count for a row, so theirs is the operator's rate
+        # (operator_tflops); achieved and frac are what the matrix cores executed,
+        # from the committed counters, and null where there are none.
         ms = stages[st][0] / args.steps
-        achieved = work[st] / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
+        operator = work[st] / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
         # translations on the FP64 matrix cores; everything else on the FP64 vector ALUs
         bound = "mfma" if st in ("m2m", "m2l", "l2l") else "alu"
         peak = FP32_PEAK_TFLOPS if (args.far_fp32 and st in ("m2l", "l2l")) else FP64_PEAK_TFLOPS
         kname = stage_kernel(st, m2l_choice)
-        traffic = measured_traffic(kname) if not args.far_fp32 else None
+        counters = measured(kname) if default_wl else {}
+        launches = stages[st][1] / args.steps
+        executed = work[st]
+        if st in ("m2m", "m2l", "l2l", "l2qbxl"):
+            flop = counters.get("f64_mfma_flop_per_dispatch") if bound == "mfma" else None
+            # (the L2L stage's first launch sums the V lists)
+            executed = flop * (launches - (st == "l2l")) if flop else None
+        achieved = executed / (ms * 1e-3) / 1e12 if executed and ms > 0 else None
         return {"bound": bound, "kernel": st, "kernel_name": kname, "achieved": achieved, "peak": peak,
-                "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
-                "algorithmic_flops_per_step": work[st], "ms_per_step": ms,
-                "launches_per_step": stages[st][1] / args.steps}
+                "unit": "TFLOP/s", "frac": achieved / peak if achieved else None,
+                "traffic": counters.get("hbm_bytes_per_dispatch"),
+                "executed_flops_per_step": executed, "algorithmic_flops_per_step": work[st],
+                "operator_tflops": operator, "ms_per_step": ms, "launches_per_step": launches}
 
     # The dominant kernel: the longest single launch of the chain on the
     # caller's stream, which bounds the step (the near field runs beside it
@@ -482,8 +500,11 @@ def main(argv=None):
         plan = qbx.Plan(g, wl.omega, wl.eps, wl.tx, wl.ty, wl.tgt_ctr,
                         qbx.options(p=wl.p, p_add=wl.p_add, leaf_max=wl.leaf_max, far_fp32=args.far_fp32))
         ab = m2l_algorithmic_bytes(plan, wl.n_dens, args.far_fp32)
-        roof["algorithmic_bytes"] = int(ab["tables"] + ab["multipoles"] + ab["locals"])
-        roof["algorithmic_bytes_pair_rows"] = int(ab["tables"] + ab["multipoles"] + ab["pair_rows"])
+        # the share of the tables that is kept, as executed (dense where not counted)
+        kept = min(1.0, roof["executed_flops_per_step"] / ab["dense_mfma_flops"]) if roof["executed_flops_per_step"] else 1.0
+        roof["kept_share"] = kept
+        roof["algorithmic_bytes"] = int(kept * ab["tables"] + ab["multipoles"] + ab["locals"])
+        roof["algorithmic_bytes_pair_rows"] = int(kept * ab["tables"] + ab["multipoles"] + ab["pair_rows"])
         roof["algorithmic_bytes_parts"] = ab
         if traffic:
             roof["traffic_over_algorithmic"] = traffic / roof["algorithmic_bytes"]
@@ -525,7 +546,8 @@ def main(argv=None):
         "ms_per_step_stages_in_order": serial_ms,
         "graph_replay": args.graph,
         "m2l_waves_per_tile": m2l_choice,
-        "stages_tflops": {k: work[k] / (v[0] / args.steps * 1e-3) / 1e12
+        # rates of the operators, entries that the kernels leave out counted in
+        "stages_operator_tflops": {k: work[k] / (v[0] / args.steps * 1e-3) / 1e12
                           for k, v in stages.items() if v[1] and v[0] > 0 and work.get(k)},
         "setup_s": setup_s,
         "err_vs_oracle_sampled": err,

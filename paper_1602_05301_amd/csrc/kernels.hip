@@ -1664,8 +1664,8 @@ __global__ void k_wsum(DevGeom g, int nd, const int *leaf_list, const int *leaf_
 // small against the wavelength an order l > 0 takes the locals of k from about
 // l on, l < 0 those up to about l, and only the block about l = 0 both.
 // Bound by FP64 issue and the LDS reads that feed it.  With every n and range
-// tests in the loop: 62 us for 32768 nodes (p = 14), 204 for four densities,
-// 321 for 200000 nodes (p = 9); now 54, 172 and 253.
+// tests in the loop: 62 us for 32768 nodes, 204 for four densities, 321 for
+// 200000 nodes (all p = 14); now 54, 164 and 255.
 // ---------------------------------------------------------------------------
 constexpr int L2Q_THREADS = 256;   // lanes per item: 16 slots x 4 l-blocks x 4 quarters
 constexpr int L2Q_PAD = 16;        // zeros around a run's locals (and around a wide J_n row)

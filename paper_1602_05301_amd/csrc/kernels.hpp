@@ -242,8 +242,9 @@ hipError_t launch_m2qbxl(const DevGeom &g, int nd, const int2 *pairs, const long
 hipError_t launch_ctr_rad(const DevGeom &g, int nleaf, double *crad, int crad_rows, hipStream_t s);
 // L2QBXL work items: L2Q_SEGS runs {c0, c1, b, level} of consecutive centres,
 // each run inside one leaf b of level >= 2 (c0 == c1: unused), at most `cap`
-// centres in all.  l2qbxl_item_cap gives the largest cap (<= L2Q_CAP_MAX) whose staging
-// fits the LDS budget for leaves of order up to Pmax and J_n rows of `rows`.
+// centres in all.  l2qbxl_item_cap gives the largest cap (<= L2Q_CAP_MAX) whose
+// staging fits half a CU's LDS for leaves of order up to Pmax and J_n rows of
+// `rows`.
 constexpr int L2Q_SEGS = 4;
 constexpr int L2Q_CAP_MAX = 16;
 constexpr int L2Q_ITEM = 4 * L2Q_SEGS;   // ints per item
